@@ -1011,10 +1011,30 @@ struct CgHead {
     double alpha, beta, rr;
     bool stop, skip;
 };
-__device__ inline CgHead cg_head(const Phys& ph, PcgState& g, bool recorder, int mem, int k,
-                                 const double* part_in, unsigned nb_in, int fresh, int maxit) {
+// What the head reads, loaded first of all in the launch: the state's scalars and
+// this thread's partials (XM as below: 3 columns at k = 0, else CG_COLS).
+template <int XM>
+struct CgIn {
+    PartLoad<XM == 0 ? 3 : (int)CG_COLS> part;
+    double bb, tol2;
+    int it_stop, skip;
+};
+template <int XM>
+__device__ inline CgIn<XM> cg_load(const Phys& ph, const PcgState& g, int mem, const double* part_in,
+                                   unsigned nb_in) {
+    CgIn<XM> in;
+    in.part = load_member<XM == 0 ? 3 : (int)CG_COLS>(part_in, nb_in, ph.batch, mem);
+    in.bb = g.bb;
+    in.tol2 = g.tol2;
+    in.it_stop = g.it_stop;
+    in.skip = g.skip;
+    return in;
+}
+template <int XM>
+__device__ inline CgHead cg_head(const CgIn<XM>& in, PcgState& g, bool recorder, int k, int fresh,
+                                 int maxit) {
     CgHead h{0.0, 0.0, 0.0, false, false};
-    if (g.skip) {
+    if (in.skip) {
         h.stop = h.skip = true;
         if (recorder) {
             g.iters = k;
@@ -1027,24 +1047,23 @@ __device__ inline CgHead cg_head(const Phys& ph, PcgState& g, bool recorder, int
     // a fresh solve, else the stored one (later refinement rounds measure
     // against the original right-hand side)
     const bool newb = fresh && k == 0;
-    double bb;
-    if (k == 0) {
+    double bb = in.bb;
+    if constexpr (XM == 0) {
         double t[3];
-        reduce_member<3, 0u, true>(part_in, nb_in, ph.batch, mem, t);
+        reduce_loaded<3, 0u, true>(in.part, t);
         h.rr = t[1];
-        bb = newb ? t[2] : g.bb;
+        if (newb) bb = t[2];
     } else {
         double t[CG_COLS];
-        reduce_member<CG_COLS, 0u, true>(part_in, nb_in, ph.batch, mem, t);
+        reduce_loaded<CG_COLS, 0u, true>(in.part, t);
         const double a = t[CG_RZ] / t[CG_PQ];
         const double rz = t[CG_RZ] - 2.0 * a * t[CG_QZ] + a * a * t[CG_QQD];
         const double rr = t[CG_RR] - 2.0 * a * t[CG_QR] + a * a * t[CG_QQ];
         h.alpha = a;
         h.beta = rz / t[CG_RZ];
         h.rr = rr < 0.0 ? 0.0 : rr;   // cancellation at the rounding floor; NaN stays NaN
-        bb = g.bb;
     }
-    const bool conv = h.rr <= g.tol2 * bb;
+    const bool conv = h.rr <= in.tol2 * bb;
     h.stop = conv || k >= maxit;
     if (recorder) {
         g.rr = h.rr;
@@ -1090,9 +1109,9 @@ __global__ void __launch_bounds__(kBlock) k_pcg_spmv(
     MEMBER(ph)
     // it_stop == k is this launch's own decision, written by the member's
     // first block: the other blocks must still take the stop path below
-    if (k > (st + mem_)->pcg.it_stop) return;
-    const CgHead h = cg_head(ph, (st + mem_)->pcg, MEMBER_FIRST(), mem_, k, part_in, nb_in, fresh,
-                             maxit);
+    const CgIn<XM> in = cg_load<XM>(ph, (st + mem_)->pcg, mem_, part_in, nb_in);
+    if (k > in.it_stop) return;
+    const CgHead h = cg_head<XM>(in, (st + mem_)->pcg, MEMBER_FIRST(), k, fresh, maxit);
     const T alpha = (T)h.alpha, beta = (T)h.beta;
     const CgX<T> xu = cg_x<T, XM>((st + mem_)->pcg, k, h.alpha, xzero);
     if (h.stop) {
@@ -1147,9 +1166,9 @@ __global__ void __launch_bounds__(TX * NTY) k_pcg_spmv_tiled(
     int fresh, int maxit, int xzero) {
     constexpr bool UPD = XM > 0, XE = XM == 2;
     MEMBER(ph)
-    if (k > (st + mem_)->pcg.it_stop) return;   // see k_pcg_spmv
-    const CgHead h = cg_head(ph, (st + mem_)->pcg, MEMBER_FIRST(), mem_, k, part_in, nb_in, fresh,
-                             maxit);
+    const CgIn<XM> in = cg_load<XM>(ph, (st + mem_)->pcg, mem_, part_in, nb_in);
+    if (k > in.it_stop) return;   // see k_pcg_spmv
+    const CgHead h = cg_head<XM>(in, (st + mem_)->pcg, MEMBER_FIRST(), k, fresh, maxit);
     const T alpha = (T)h.alpha, beta = (T)h.beta;
     const T inv_h2 = (T)ph.inv_h2;
     const int n = ph.n, cz = ph.cz;
@@ -1391,6 +1410,7 @@ __global__ void __launch_bounds__(64 * kRowWaves) k_pcg_spmv_rows(
     static_assert(H == 1 ? kRowWaves >= 6 : H == 2 && kRowWaves == 8,
                   "y halo loads: wavefronts 0-5 (one per row) or 0-7 (two per row)");
     MEMBER(ph)
+    const CgIn<XM> in = cg_load<XM>(ph, (st + mem_)->pcg, mem_, part_in, nb_in);
     const int n = ph.n, cz = ph.cz;   // n == 64 V
     constexpr int TY = kRowWaves / H, RW = 64 * H;   // rows per block, lanes per row
     const int lane = threadIdx.x, wv = threadIdx.y;
@@ -1458,9 +1478,8 @@ __global__ void __launch_bounds__(64 * kRowWaves) k_pcg_spmv_rows(
     VT rnx = ld(rin, Q1), qnx = ldu(qold, Q1), dnx = ld(diag, Q1), onx = ldu(pold, Q1);
     VT h1 = ld(hsrc, hc1 + plane(k0)), h2 = ld(hdsrc, hc2 + plane(k0));
     VT h3 = ldu(hosrc, hc3 + plane(k0)), h4 = ldu(hqsrc, hc4 + plane(k0));
-    if (k > (st + mem_)->pcg.it_stop) return;   // see k_pcg_spmv
-    const CgHead h = cg_head(ph, (st + mem_)->pcg, MEMBER_FIRST(), mem_, k, part_in, nb_in, fresh,
-                             maxit);
+    if (k > in.it_stop) return;   // see k_pcg_spmv
+    const CgHead h = cg_head<XM>(in, (st + mem_)->pcg, MEMBER_FIRST(), k, fresh, maxit);
     const T alpha = (T)h.alpha, beta = (T)h.beta;
     const T inv_h2 = (T)ph.inv_h2;
     const CgX<T> xu = cg_x<T, XM>((st + mem_)->pcg, k, h.alpha, xzero);
