@@ -255,8 +255,8 @@ constexpr unsigned kXcds = 8;   // accelerator complex dies, each with its own L
 // reduction partials are all indexed by the logical number.
 __device__ inline unsigned flat_bid() {
     const unsigned f = blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z);
-    const unsigned B = num_blocks();
-    return B % kXcds == 0 ? (f % kXcds) * (B / kXcds) + f / kXcds : f;
+    const unsigned B = num_blocks(), q = B / kXcds, r = B % kXcds, x = f % kXcds;
+    return x * q + (x < r ? x : r) + f / kXcds;   // the first r XCDs hold one block more
 }
 
 // Logical 3D block coordinates (x fastest) of this block.

@@ -1152,8 +1152,7 @@ __global__ void __launch_bounds__(kBlock) k_pcg_spmv(
 }
 
 // Tiled form: a block of TX x NTY threads owns a TX x (NTY RPT) column tile
-// (64 x 8 for n a multiple of 64, 16 x 16 for the other multiples of 16) and
-// marches along z.  Each of r, q, p_old, diag and w is read once per cell
+// (n a multiple of 64) and marches along z.  Each of r, q, p_old, diag and w is read once per cell
 // from HBM: the x-y neighbours of the current plane come from LDS tiles (halo
 // 2 for w; halo 1 for the direction p, formed from r, q, p_old and diag at
 // the halo cells), the z neighbours from per-thread register queues.
@@ -1629,6 +1628,191 @@ __global__ void __launch_bounds__(64 * kRowWaves) k_pcg_spmv_rows(
         zc = zp;
         ic = ip;
         dc = dn;
+    }
+    block_partials<CG_COLS, 0u, true>(acc, part_out);
+}
+
+// Flat form (any n with flat_rows(n) >= 2): a block owns R consecutive full
+// x-rows of a plane (R = ceil(n / gridDim.y); the last block of a plane may own
+// fewer), one cell per thread over the flattened rows, and marches along z over
+// cz planes.  Rows of any length fill the wavefronts (64-wide tiles left half
+// the lanes idle at n = 70), and as in the row form no x halo is read: periodic
+// neighbours come from the row's LDS copy.  The y halo (2 rows of w and 1 of p
+// on each side) is loaded by the block's own threads, the p halo by threads
+// t < 2 n, the w halo (4 n cells, HW per thread) from the last thread down, so
+// that few threads carry both.  Threads past the last row repeat the block's
+// first cell and store nothing.  The z neighbours come from register queues;
+// loads past the chunk's last needed plane are clamped to planes already read.
+// Bound: latency.  At 32^3 a launch is the chain state and partials -> totals
+// -> p -> barrier -> q -> totals, at 70^3 the march over 2-3 planes; only from
+// 128^3 on does it come near the fabric's rate.  us per iteration, launch gap
+// included, against the form each size had before (FP64; FP32): 32^3 9.9
+// against 15.7 (16 x 16 tiles; 6.7, 10.6), 70^3 13.9 against 30 (gathered;
+// 9.1, 17), 100^3 23.6 against 46 (13.0, 26.6), 160^3 84 against 89 (31.5,
+// 51), 192^3 130 against 140 (64 x 16 tiles; 58.5, 58.9), 250^3 263 against 538
+// (123, 248).
+template <typename T, int XM, int HW, int MT>
+__global__ void __launch_bounds__(MT, 4) k_pcg_spmv_flat(
+    Phys ph, DevState* st, int k, const T* __restrict__ rin, T* __restrict__ rout,
+    const T* __restrict__ diag, const T* __restrict__ w, const T* __restrict__ pold,
+    const T* __restrict__ pold2, T* __restrict__ pnew, const T* __restrict__ qold,
+    T* __restrict__ q, T* __restrict__ x, const double* part_in, unsigned nb_in, double* part_out,
+    int fresh, int maxit, int xzero) {
+    constexpr bool UPD = XM > 0, XE = XM == 2;
+    MEMBER(ph)
+    extern __shared__ __align__(16) unsigned char flat_lds[];
+    const CgIn<XM> in = cg_load<XM>(ph, (st + mem_)->pcg, mem_, part_in, nb_in);
+    const int n = ph.n, cz = ph.cz;
+    const int B = blockDim.x, tid = threadIdx.x;
+    const int R = (n + (int)gridDim.y - 1) / (int)gridDim.y;
+    const int j0 = bp_.y * R;
+    const int rows = n - j0 < R ? n - j0 : R;
+    const int k0 = bz_ * cz;
+    const int k1 = k0 + cz < n ? k0 + cz : n;
+    const size_t nn = (size_t)n * n;
+    // the rows of a plane in two sets alternating with the plane's parity (one
+    // barrier per plane, as in the row form): w of rows j0-2 .. j0+rows+1,
+    // p of rows j0-1 .. j0+rows
+    const int wsz = (R + 4) * n, psz = (R + 2) * n;
+    T* const wl0 = reinterpret_cast<T*>(flat_lds);
+    T* const pl0 = wl0 + 2 * wsz;
+    auto wr = [n](int a) { return a < 0 ? a + n : (a >= n ? a - n : a); };
+    auto plane = [&](int kk) { return nn * (size_t)wr(kk); };
+    const bool act = tid < rows * n;
+    const int y = act ? tid / n : 0, xi = act ? tid - y * n : 0;
+    const size_t col = base_ + (size_t)n * (j0 + y) + xi;
+    const int ow = (y + 2) * n, op = (y + 1) * n;   // this row in LDS
+    const int xm1 = wr(xi - 1), xm2 = wr(xi - 2), xp1 = wr(xi + 1), xp2 = wr(xi + 2);
+    // halo cells: position in a plane (own cell if none) and LDS slot
+    const bool hasp = tid < 2 * n;
+    const int hpx = tid < n ? tid : tid - n;
+    const size_t hpc = hasp ? base_ + (size_t)n * wr(tid < n ? j0 - 1 : j0 + rows) + hpx : col;
+    const int hps = (tid < n ? 0 : rows + 1) * n + hpx;
+    size_t hwc[HW];
+    int hws[HW];
+#pragma unroll
+    for (int m = 0; m < HW; ++m) {
+        const int u = B - 1 - tid + m * B;
+        const int s4 = u / n, hx = u - s4 * n;
+        const bool has = s4 < 4;
+        hwc[m] = has ? base_ + (size_t)n * wr(s4 < 2 ? j0 - 2 + s4 : j0 + rows + s4 - 2) + hx : col;
+        hws[m] = has ? (s4 < 2 ? s4 : rows + s4) * n + hx : -1;
+    }
+    auto ldu = [&](const T* f, size_t o) -> T { return UPD ? f[o] : T(0); };
+    // the first planes' loads go out before the launch's serial head
+    const T wmm = w[col + plane(k0 - 2)];
+    T wm1 = w[col + plane(k0 - 1)], w0 = w[col + plane(k0)], wp1 = w[col + plane(k0 + 1)];
+    T wp2n = w[col + plane(k0 + 2)];
+    const size_t Qm = col + plane(k0 - 1), Q0 = col + plane(k0), Q1 = col + plane(k0 + 1);
+    const T rm_in = rin[Qm], qm_in = ldu(qold, Qm), dm_in = diag[Qm], om_in = ldu(pold, Qm);
+    T oc = ldu(pold, Q0), dc = diag[Q0];
+    const T r0_in = rin[Q0], q0_in = ldu(qold, Q0);
+    T xc = XE ? x[Q0] : T(0), xn1 = xc;
+    T o2c = XE ? pold2[Q0] : T(0), o2n1 = o2c;
+    T rnx = rin[Q1], qnx = ldu(qold, Q1), dnx = diag[Q1], onx = ldu(pold, Q1);
+    T hr = rin[hpc + plane(k0)], hd = diag[hpc + plane(k0)];
+    T hq = ldu(qold, hpc + plane(k0)), ho = ldu(pold, hpc + plane(k0));
+    T hw[HW];
+#pragma unroll
+    for (int m = 0; m < HW; ++m) hw[m] = w[hwc[m] + plane(k0)];
+    if (k > in.it_stop) return;   // see k_pcg_spmv
+    const CgHead h = cg_head<XM>(in, (st + mem_)->pcg, MEMBER_FIRST(), k, fresh, maxit);
+    const T alpha = (T)h.alpha, beta = (T)h.beta;
+    const T inv_h2 = (T)ph.inv_h2;
+    const CgX<T> xu = cg_x<T, XM>((st + mem_)->pcg, k, h.alpha, xzero);
+    if (h.stop) {
+        if ((UPD || xzero) && !h.skip && act) {
+            for (int kk = k0; kk < k1; ++kk) {
+                const size_t Q = col + nn * (size_t)kk;
+                x[Q] = XE ? xu.two(x[Q], pold2[Q], pold[Q]) : UPD ? xu.one(x[Q], pold[Q]) : T(0);
+            }
+        }
+        return;
+    }
+    // r_k and p_k of a cell from its r_{k-1}, q_{k-1}, diag, p_{k-1}
+    auto resf = [&](T ro, T qo) -> T { return UPD ? ro - alpha * qo : ro; };
+    auto dirf = [&](T z, T po) -> T { return UPD ? z + beta * po : z; };
+    T pm = dirf(resf(rm_in, qm_in) * jinv(dm_in), om_in);
+    T rc = resf(r0_in, q0_in);
+    T ic = jinv(dc), zc = rc * ic;
+    T pc = dirf(zc, oc);
+    T kzm = (T(9) * (wm1 + w0) - (wmm + wp1)) * T(0.0625);
+    double acc[CG_COLS] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+    for (int kk = k0; kk < k1; ++kk) {
+        const T wp2 = wp2n;
+        const T rp = resf(rnx, qnx);
+        const T dn = dnx, on = onx;
+        const T ip = jinv(dn), zp = rp * ip;
+        const T pp = dirf(zp, on);
+        T* const wl = wl0 + (kk & 1) * wsz;
+        T* const pl = pl0 + (kk & 1) * psz;
+        if (act) {
+            wl[ow + xi] = w0;
+            pl[op + xi] = pc;
+        }
+        if (hasp) pl[hps] = dirf(resf(hr, hq) * jinv(hd), ho);
+#pragma unroll
+        for (int m = 0; m < HW; ++m)
+            if (hws[m] >= 0) wl[hws[m]] = hw[m];
+        {
+            const int kw = kk + 3 < k1 + 1 ? kk + 3 : k1 + 1;   // last w plane needed: k1 + 1
+            const int kp = kk + 2 < k1 ? kk + 2 : k1;           // last p plane needed: k1
+            const int kh = kk + 1 < k1 - 1 ? kk + 1 : k1 - 1;   // last halo plane: k1 - 1
+            const size_t Qp = col + plane(kp), Qh = plane(kh);
+            wp2n = w[col + plane(kw)];
+            rnx = rin[Qp];
+            qnx = ldu(qold, Qp);
+            dnx = diag[Qp];
+            onx = ldu(pold, Qp);
+            hr = rin[hpc + Qh];
+            hd = diag[hpc + Qh];
+            hq = ldu(qold, hpc + Qh);
+            ho = ldu(pold, hpc + Qh);
+#pragma unroll
+            for (int m = 0; m < HW; ++m) hw[m] = w[hwc[m] + Qh];
+            if (XE) {
+                const size_t Qx = col + Qh;
+                xn1 = x[Qx];
+                o2n1 = pold2[Qx];
+            }
+        }
+        lds_barrier();
+        const T xw1 = wl[ow + xm1], xw2 = wl[ow + xm2], xe1 = wl[ow + xp1], xe2 = wl[ow + xp2];
+        const T ys1 = wl[ow - n + xi], ys2 = wl[ow - 2 * n + xi];
+        const T yn1 = wl[ow + n + xi], yn2 = wl[ow + 2 * n + xi];
+        const T kxp = (T(9) * (w0 + xe1) - (xw1 + xe2)) * T(0.0625);
+        const T kxm = (T(9) * (xw1 + w0) - (xw2 + xe1)) * T(0.0625);
+        const T kyp = (T(9) * (w0 + yn1) - (ys1 + yn2)) * T(0.0625);
+        const T kym = (T(9) * (ys1 + w0) - (ys2 + yn1)) * T(0.0625);
+        const T kzp = (T(9) * (w0 + wp1) - (wm1 + wp2)) * T(0.0625);
+        const T lap = kxp * (pc - pl[op + xp1]) + kxm * (pc - pl[op + xm1]) +
+                      kyp * (pc - pl[op + n + xi]) + kym * (pc - pl[op - n + xi]) +
+                      kzp * (pc - pp) + kzm * (pc - pm);
+        const T sumK = kxp + kxm + kyp + kym + kzp + kzm;
+        const T qv = (dc - sumK * inv_h2) * pc + lap * inv_h2;
+        if (act) {
+            const size_t P = col + nn * (size_t)kk;
+            q[P] = qv;
+            pnew[P] = pc;
+            if (UPD) rout[P] = rc;
+            if (XE) x[P] = xu.two(xc, o2c, oc);
+            cg_accumulate(acc, pc, qv, rc, zc, ic);
+        }
+        wm1 = w0;
+        w0 = wp1;
+        wp1 = wp2;
+        kzm = kzp;
+        pm = pc;
+        pc = pp;
+        rc = rp;
+        zc = zp;
+        ic = ip;
+        dc = dn;
+        if (UPD) oc = on;
+        if (XE) {
+            xc = xn1;
+            o2c = o2n1;
+        }
     }
     block_partials<CG_COLS, 0u, true>(acc, part_out);
 }
@@ -3847,19 +4031,34 @@ Launch make_spmv_launch(int n, int batch, int elem_bytes, int cz_tile) {
         return L;
     }
     const int TY = kTY * spmv_rows(elem_bytes);
-    const bool wide = n >= 64 && n % kTX == 0 && n % TY == 0;
-    if (!wide && n % kSmallTX != 0) return L;   // nblocks = 0: not available
-    const int tx = wide ? kTX : kSmallTX, ty = wide ? TY : kSmallTX;
-    const int gx = n / tx, gy = n / ty;
-    int nz = kTiledBlocks / (gx * gy);
-    nz = nz < 1 ? 1 : nz;
+    if (n > kFlatBeforeTiles && n % kTX == 0 && n % TY == 0) {
+        const int gx = n / kTX, gy = n / TY;
+        int nz = kTiledBlocks / (gx * gy);
+        nz = nz < 1 ? 1 : nz;
+        int cz = (n + nz - 1) / nz;
+        if (cz < 8) cz = 8;
+        if (cz_tile > 0) cz = cz_tile < n ? cz_tile : n;
+        nz = (n + cz - 1) / cz;
+        L.block = dim3(kTX, kTY, 1);
+        L.grid = dim3(gx, gy, nz * batch);
+        L.nblocks = L.grid.x * L.grid.y * L.grid.z;
+        L.cz = cz;
+        L.nz = nz;
+        return L;
+    }
+    int rows = flat_rows(n, elem_bytes);
+    if (rows < 2) return L;   // nblocks = 0: not available
+    const int gy = (n + rows - 1) / rows;
+    rows = (n + gy - 1) / gy;
+    int nz = (n > 256 ? 2 * kFlatBlocks : kFlatBlocks) / gy;
+    nz = nz < 1 ? 1 : nz > n ? n : nz;
     int cz = (n + nz - 1) / nz;
-    if (cz < 8) cz = 8;   // 4 or 2 planes: slower at 32^3-48^3 (z halo, launch of more blocks)
     if (cz_tile > 0) cz = cz_tile < n ? cz_tile : n;
     nz = (n + cz - 1) / cz;
-    L.block = wide ? dim3(kTX, kTY, 1) : dim3(kSmallTX, kSmallTX, 1);
-    L.grid = dim3(gx, gy, nz * batch);
-    L.nblocks = L.grid.x * L.grid.y * L.grid.z;
+    L.rows = rows;
+    L.block = dim3((rows * n + 63) / 64 * 64, 1, 1);
+    L.grid = dim3(1, gy, nz * batch);
+    L.nblocks = L.grid.y * L.grid.z;
     L.cz = cz;
     L.nz = nz;
     return L;
@@ -4039,14 +4238,29 @@ static void spmv_launch(const Launch& L, const Launch& TL, hipStream_t s, const 
         }
         return;
     }
+    if (TL.nblocks && TL.rows) {
+        Phys pt = ph;
+        pt.cz = TL.cz;
+        pt.nz = TL.nz;
+        const size_t lds = flat_cg_lds(ph.n, TL.rows, sizeof(T));
+        const bool one = 4u * ph.n <= TL.block.x;
+#define FLAT(HW, MT) \
+    hipLaunchKernelGGL((k_pcg_spmv_flat<T, XM, HW, MT>), TL.grid, TL.block, lds, s, pt, SPMV_ARGS)
+        if (TL.block.x <= 512) {
+            if (one) FLAT(1, 512);
+            else FLAT(2, 512);
+        } else {
+            if (one) FLAT(1, 1024);
+            else FLAT(2, 1024);
+        }
+#undef FLAT
+        return;
+    }
     if (TL.nblocks) {
         Phys pt = ph;
         pt.cz = TL.cz;
         pt.nz = TL.nz;
-        if (TL.block.x == kSmallTX)
-            LAUNCH((k_pcg_spmv_tiled<T, 1, XM, kSmallTX, kSmallTX>), TL, s, pt, SPMV_ARGS);
-        else
-            LAUNCH((k_pcg_spmv_tiled<T, spmv_rows(sizeof(T)), XM, kTX, kTY>), TL, s, pt, SPMV_ARGS);
+        LAUNCH((k_pcg_spmv_tiled<T, spmv_rows(sizeof(T)), XM, kTX, kTY>), TL, s, pt, SPMV_ARGS);
     } else {
         LAUNCH((k_pcg_spmv<T, XM>), L, s, ph, SPMV_ARGS);
     }

@@ -18,6 +18,7 @@ struct Launch {
     int nz;             // blocks per member along z
     int v = 0;          // CG kernel: cells per lane along x of the full-row form (0: tiles)
     int h = 0;          // and wavefronts per x-row
+    int rows = 0;       // and x-rows per block of its flat form (0: another form)
     bool nt = false;    // and its once-read fields streamed past the caches (make_spmv_launch)
 };
 
@@ -45,14 +46,15 @@ Launch make_tiled_launch(int n, int batch = 1, int cz_tile = 0);
 //   256 one wavefront per x-row and 4 cells per lane in FP32, two per x-row and
 //   2 cells per lane in FP64 (4 doubles per lane spill registers); at 128 one
 //   wavefront per x-row and 2 cells per lane.
-// * Other multiples of 64 (and of 8 spmv_rows): tiles of 64 x (8 spmv_rows)
-//   cells, 64 x 8 threads each owning spmv_rows rows (v = 0; two rows in FP64
-//   halve the tile's y halo; in FP32 two measured no faster).
-// * Other multiples of kSmallTX: tiles of kSmallTX x kSmallTX cells, one thread
-//   per column (block.x = kSmallTX).
+// * Multiples of 64 from 320 on: tiles of 64 x (8 spmv_rows) cells, 64 x 8
+//   threads each owning spmv_rows rows (v = 0; two rows in FP64 halve the
+//   tile's y halo; in FP32 two measured no faster).  At 320 the flat form took
+//   643 against 549 us in FP64 (272 against 255 in FP32): three rows per block
+//   leave it a y halo as large as the tile; at 192 and below it is the faster.
+// * Every other n with flat_rows(n) >= 2: the flat form, rows x-rows per block.
 // nblocks is 0 when none is available.  Tiles march over at least 8 planes, or
-// exactly min(cz_tile, n) when cz_tile > 0 (a tuned choice; the full-row form
-// ignores it).
+// like the flat form over exactly min(cz_tile, n) when cz_tile > 0 (a tuned
+// choice; the full-row form ignores it).
 // nt (full-row form): the fields a CG iteration reads once (r, q, p_old of the
 // main rows) are loaded non-temporally, so that w and diag, which every
 // iteration of a solve reads again, stay in the memory-side cache (kMallBytes)
@@ -61,7 +63,28 @@ Launch make_tiled_launch(int n, int batch = 1, int cz_tile = 0);
 // 5 % less time; in FP64 (w and diag 268 MB) it took 8 % more.
 constexpr double kMallBytes = 256.0 * 1024 * 1024;
 constexpr int spmv_rows(int elem_bytes) { return elem_bytes == 8 ? 2 : 1; }
-constexpr int kSmallTX = 16;
+constexpr int kFlatBeforeTiles = 256;
+// Rows per block of the flat form: as many as fit 512 threads up to n = 64, 768
+// up to 100, 1024 beyond (larger blocks read less halo; smaller ones spread the
+// same planes over more CUs and shorter marches), but at least 8 blocks per plane
+// up to n = 40, where whole planes would leave CUs idle.  z is then cut for one
+// block per CU (kFlatBlocks, two from n = 257 on), so that no block waits for
+// another to end and the launch's head totals few partials: of the shapes
+// swept at 24 sizes from 16 to 336 in both precisions the rule's is within
+// 10 % of the fastest, and half or twice as many blocks take 5-40 % longer.
+// The block's LDS (two plane sets of R + 4 rows of w and R + 2 of p) stays
+// within kFlatLds beside the reduction's.
+constexpr int kFlatBlocks = 256;
+constexpr size_t kFlatLds = 60 * 1024;
+constexpr size_t flat_cg_lds(int n, int rows, int elem_bytes) {
+    return (size_t)2 * (2 * rows + 6) * n * elem_bytes;
+}
+constexpr int flat_rows(int n, int elem_bytes) {
+    int r = (n <= 64 ? 512 : n <= 100 ? 768 : 1024) / n;
+    if (n <= 40) r = n <= 16 ? 2 : (n + 7) / 8;
+    while (r >= 2 && flat_cg_lds(n, r, elem_bytes) > kFlatLds) --r;
+    return r;
+}
 constexpr int kRowWaves = 8, kRowBlocks = 256;
 // Wavefronts per x-row of the full-row CG form for n and elem_bytes (0: none).
 constexpr int row_waves(int n, int elem_bytes) {
