@@ -14,8 +14,6 @@ namespace pisoc {
 
 constexpr int kNetWeights = 15120;   // 27 (2*16 + 16*16 + 16*16 + 16*1)
 
-// Offset of layer l in the FP32 weight vector (layer-major, [co][ci][27]).
-size_t net_weight_offset(int layer);
 // Bytes of the packed BF16 MFMA operands of the four forward layers.
 size_t net_packed_bytes();
 // Pack FP32 weights into per-lane BF16 MFMA operands (device to device).
