@@ -3226,6 +3226,201 @@ __global__ void __launch_bounds__(kTX * kTY) k_tiled(Phys ph, DevState* st, K ke
     if (MEMBER_FIRST()) k.first(st + mem_);
 }
 
+// The same on flattened full x-rows, for the smaller grids and those that the
+// 64 x 8 tiles do not divide (flat_field_rows): as in the CG kernel's flat form a
+// block owns R whole
+// rows of a plane, one cell per thread, R = ceil(n / gridDim.y), and marches
+// along z.  The x neighbours come from the row's periodic LDS copy, the y
+// neighbours from LDS rows with a halo of two, the z neighbours from a
+// five-plane register queue.  K::XS, K::YS and K::ZS name the stencil fields read
+// along each axis (a corrector set-up reads the HbyA components along one axis
+// each).  Halo values and the cell's own values are loaded a plane ahead, queue
+// heads two; loads past the chunk's last needed plane are clamped.
+// Bound: the planes' load latency with one 512-thread block (FP64) per CU; the
+// gathered kernels re-read each stencil through the caches with 64-wide
+// wavefronts, 35 % of whose lanes idle at n = 100.  us per launch in FP64, before
+// and now: momentum sweep 24.1 and 13.8 at 70^3, 42.7 and 28.9 at 100^3; a step's
+// field kernels in all 382 and 247, 700 and 511 (FP32 237 and 202, 378 and 369);
+// at 64^3, where the tiles' 8-plane minimum left 64 blocks, an FP64 step took 662
+// us on tiles and takes 476.
+template <typename T, class K>
+__global__ void __launch_bounds__(kFlatFieldThreads) k_flat(Phys ph, DevState* st, K kern) {
+    MEMBER(ph)
+    extern __shared__ __align__(16) unsigned char flat_lds[];
+    constexpr int NS = K::NS;
+    constexpr bool FACES = K::FACES;
+    constexpr int NRA = K::NR > 0 ? K::NR : 1;
+    constexpr unsigned XS = K::XS, YS = K::YS, ZS = K::ZS;
+    constexpr int NY = __builtin_popcount(YS & ((1u << NS) - 1u));
+    // halo cells per row of n: 4 per field read along y, 1 of the y faces; a
+    // block has at least kFlatFieldRows rows
+    constexpr int kPer = (4 * NY + (FACES ? 1 : 0) + kFlatFieldRows - 1) / kFlatFieldRows;
+    constexpr int kPerA = kPer > 0 ? kPer : 1;
+    const size_t N = ncell(ph);
+    K k = kern;
+    k.member(ph, st + mem_);
+    if (MEMBER_FIRST()) k.lead(st + mem_);   // state a launch records even when it skips
+    if (k.skip(st + mem_)) return;           // whole block, before any barrier
+    const int n = ph.n, cz = ph.cz;
+    const int B = blockDim.x, tid = threadIdx.x;
+    const int R = (n + (int)gridDim.y - 1) / (int)gridDim.y;
+    const int j0 = bp_.y * R;
+    const int rows = n - j0 < R ? n - j0 : R;
+    const int k0 = bz_ * cz;
+    const int k1 = k0 + cz < n ? k0 + cz : n;
+    const size_t nn = (size_t)n * n;
+    auto wr = [n](int a) { return a < 0 ? a + n : (a >= n ? a - n : a); };
+    auto clampk = [](int a, int hi) { return a < hi ? a : hi; };
+    // LDS: R + 4 rows of each stencil field, the x faces' R rows, the y faces'
+    // R + 1 rows (from y = j0 - 1 on)
+    T* const U = reinterpret_cast<T*>(flat_lds);
+    const int us = (R + 4) * n;
+    T* const FX = U + NS * us;
+    T* const FY = FX + R * n;
+    const bool act = tid < rows * n;
+    const int y = act ? tid / n : 0, xi = act ? tid - y * n : 0;
+    const size_t col = base_ + (size_t)n * (j0 + y) + xi;
+    const int ow = (y + 2) * n;
+    const int xm1 = wr(xi - 1), xm2 = wr(xi - 2), xp1 = wr(xi + 1), xp2 = wr(xi + 2);
+    typedef const T __attribute__((address_space(1)))* gptr;   // global memory
+    gptr hsrc[kPerA];
+    size_t hoff[kPerA];
+    int hdst[kPerA];
+#pragma unroll
+    for (int q = 0; q < kPer; ++q) {
+        const int jb = tid + q * B;
+        hsrc[q] = (gptr)k.sf[0];
+        hoff[q] = col;
+        hdst[q] = -1;
+        const int h = jb / n, hx = jb - h * n;      // halo row h of the job list
+        int f = -1, at = 0;                         // its field
+#pragma unroll
+        for (int g = 0; g < NS; ++g)
+            if ((YS >> g) & 1u) {
+                if (h >= 4 * at && h < 4 * at + 4) {
+                    f = g;
+                    hsrc[q] = (gptr)k.sf[g];
+                }
+                ++at;
+            }
+        if (f >= 0) {                               // rows j0-2, j0-1, j0+rows, j0+rows+1
+            const int r4 = h & 3, yy = r4 < 2 ? r4 : rows + r4;
+            hoff[q] = base_ + (size_t)hx + (size_t)n * wr(j0 - 2 + yy);
+            hdst[q] = f * us + yy * n + hx;
+        } else if (FACES && h == 4 * NY) {          // face y at y = j0 - 1
+            hsrc[q] = (gptr)(k.face + N);
+            hoff[q] = base_ + (size_t)hx + (size_t)n * wr(j0 - 1);
+            hdst[q] = NS * us + R * n + hx;
+        }
+    }
+    // the z queues (fields read along z: planes kk - 2 .. kk + 2; others: slot 2 only)
+    T q5[NS][5], fzq[2] = {T(0), T(0)}, cfx = T(0), cfy = T(0), nh[kPerA];
+#pragma unroll
+    for (int f = 0; f < NS; ++f)
+#pragma unroll
+        for (int t = 0; t < 5; ++t)
+            q5[f][t] = ((ZS >> f) & 1u) || t == 2 ? k.sf[f][col + nn * wr(k0 - 2 + t)] : T(0);
+    if (FACES) {
+        fzq[0] = k.face[2 * N + col + nn * wr(k0 - 1)];
+        fzq[1] = k.face[2 * N + col + nn * k0];
+        cfx = k.face[col + nn * k0];
+        cfy = k.face[N + col + nn * k0];
+    }
+    typename K::Pts cur = k.load(col + nn * k0), nxt;
+#pragma unroll
+    for (int q = 0; q < kPer; ++q) nh[q] = hsrc[q][nn * (size_t)k0 + hoff[q]];
+    T nq[NS], nfz = T(0), nfx = T(0), nfy = T(0);
+    // queue heads at plane kq, own values at kv
+    auto prefetch = [&](int kq, int kv) {
+        const size_t p5 = nn * (size_t)wr(kq), pv = nn * (size_t)kv;
+#pragma unroll
+        for (int f = 0; f < NS; ++f) nq[f] = k.sf[f][col + (((ZS >> f) & 1u) ? p5 : pv)];
+        if (FACES) {
+            nfz = k.face[2 * N + col + pv];
+            nfx = k.face[col + pv];
+            nfy = k.face[N + col + pv];
+        }
+        nxt = k.load(col + pv);
+    };
+    prefetch(clampk(k0 + 3, k1 + 1), clampk(k0 + 1, k1 - 1));
+    double acc[NRA];
+    k.init(acc);
+    for (int kk = k0; kk < k1; ++kk) {
+        if (act) {
+#pragma unroll
+            for (int f = 0; f < NS; ++f)
+                if (((XS | YS) >> f) & 1u) U[f * us + ow + xi] = q5[f][2];
+            if (FACES) {
+                FX[y * n + xi] = cfx;
+                FY[(y + 1) * n + xi] = cfy;
+            }
+        }
+#pragma unroll
+        for (int q = 0; q < kPer; ++q)
+            if (hdst[q] >= 0) U[hdst[q]] = nh[q];
+        const size_t hp = nn * (size_t)clampk(kk + 1, k1 - 1);
+#pragma unroll
+        for (int q = 0; q < kPer; ++q) nh[q] = hsrc[q][hp + hoff[q]];
+        lds_barrier();
+        T v[NS][13], fp[3], fm[3];
+#pragma unroll
+        for (int f = 0; f < NS; ++f) {
+            const T* u = U + f * us + ow;
+            v[f][0] = q5[f][2];
+            if ((XS >> f) & 1u) {
+                v[f][1] = u[xm2];
+                v[f][2] = u[xm1];
+                v[f][3] = u[xp1];
+                v[f][4] = u[xp2];
+            }
+            if ((YS >> f) & 1u) {
+                v[f][5] = u[xi - 2 * n];
+                v[f][6] = u[xi - n];
+                v[f][7] = u[xi + n];
+                v[f][8] = u[xi + 2 * n];
+            }
+            if ((ZS >> f) & 1u) {
+                v[f][9] = q5[f][0];
+                v[f][10] = q5[f][1];
+                v[f][11] = q5[f][3];
+                v[f][12] = q5[f][4];
+            }
+        }
+        if (FACES) {
+            fp[0] = cfx;
+            fm[0] = FX[y * n + xm1];
+            fp[1] = cfy;
+            fm[1] = FY[y * n + xi];
+            fp[2] = fzq[1];
+            fm[2] = fzq[0];
+        }
+        lds_barrier();
+        if (act) k.cell(col + nn * (size_t)kk, v, fp, fm, cur, acc);
+        // advance the queues with the values loaded a plane ago, then load the
+        // queue heads at kk + 4 and the values of plane kk + 2
+#pragma unroll
+        for (int f = 0; f < NS; ++f) {
+            if ((ZS >> f) & 1u) {
+#pragma unroll
+                for (int t = 0; t < 4; ++t) q5[f][t] = q5[f][t + 1];
+                q5[f][4] = nq[f];
+            } else {
+                q5[f][2] = nq[f];
+            }
+        }
+        if (FACES) {
+            fzq[0] = fzq[1];
+            fzq[1] = nfz;
+            cfx = nfx;
+            cfy = nfy;
+        }
+        cur = nxt;
+        prefetch(clampk(kk + 4, k1 + 1), clampk(kk + 2, k1 - 1));
+    }
+    if constexpr (K::NR > 0) block_partials<K::NR, K::MASK>(acc, k.part);
+    if (MEMBER_FIRST()) k.first(st + mem_);
+}
+
 // The 13-point cross v of a field: the line of five cells along d (as
 // gather_line) and the 7-point cross (as gather7).
 template <typename T>
@@ -3255,6 +3450,8 @@ struct TiledBase {
     static constexpr bool FACES = false;
     static constexpr int NR = 0;
     static constexpr unsigned MASK = 0u;
+    // the stencil fields read along x, y and z (k_flat)
+    static constexpr unsigned XS = ~0u, YS = ~0u, ZS = ~0u;
     const T* face = nullptr;
     double* part = nullptr;
     size_t NT = 0;
@@ -3970,11 +4167,119 @@ struct TiledPredict : TiledBase<T> {
     }
 };
 
-// Launch of k_tiled over the tiled launch TL; returns its block count (the
-// number of partials a reducing functor writes).
+// The momentum sweep and H/A (k_mom_sweep) on flattened rows.
+template <typename T, bool HBYA>
+struct FlatMomSweep : TiledBase<T> {
+    static constexpr int NS = HBYA ? 3 : 4;   // u_x, u_y, u_z (and p^n)
+    static constexpr bool FACES = true;       // the convecting flux
+    const T* sf[NS];
+    const T *aP, *s, *rk;
+    T *out, *w, *p0;
+    T inv_V, inv_h, mu_h2;
+    double rref, pref, gamma, Rg;
+    const double* ts;                         // Fourier closure: T* (else null)
+    struct Pts { T a, s[3], rk; };
+    __device__ void member(const Phys& ph, const DevState* d) {
+        this->NT = ph.NT;
+        inv_V = (T)ph.inv_V;
+        inv_h = (T)ph.inv_h;
+        mu_h2 = (T)(ph.mu * ph.inv_h2);
+        rref = d->rho_ref;
+        pref = d->p_ref;
+        gamma = ph.gamma;
+        Rg = ph.R;
+        ts = ph.fourier ? ph.ts : nullptr;
+    }
+    __device__ Pts load(size_t P) const {
+        return {stream_ld(aP + P),
+                {stream_ld(s + P), stream_ld(s + this->NT + P), stream_ld(s + 2 * this->NT + P)},
+                HBYA ? stream_ld(rk + P) : T(0)};
+    }
+    __device__ void cell(size_t P, const T (&v)[NS][13], const T (&fp)[3], const T (&fm)[3],
+                         const Pts& p, double*) const {
+        T u[3][13], o[3], ia;
+#pragma unroll
+        for (int m = 0; m < 3; ++m)
+#pragma unroll
+            for (int t = 0; t < 13; ++t) u[m][t] = v[m][t];
+        mom_cell<T, HBYA>(u, v[NS - 1], fp, fm, p.s, p.a, inv_V, inv_h, mu_h2, o, ia);
+#pragma unroll
+        for (int m = 0; m < 3; ++m) stream_st(out + (m * this->NT + P), o[m]);
+        if (HBYA) {
+            stream_st(w + P, ((T)rref + p.rk) * ia);
+            stream_st(p0 + P, ts ? (T)((rref + (double)p.rk) * Rg * ts[P] - pref)
+                                 : pdev(p.rk, rref, pref, gamma));
+        }
+    }
+};
+
+// The corrector set-up (k_corr_rhs) on flattened rows.
+template <typename T>
+struct FlatCorrRhs : TiledBase<T> {
+    static constexpr int NS = 6;          // w, rho_k, HbyA_x, HbyA_y, HbyA_z, p0
+    static constexpr unsigned XS = 0b100111u, YS = 0b101011u, ZS = 0b110011u;
+    static constexpr int NR = 3;
+    const T* sf[6];
+    const T* rn;
+    T *phiH, *rvec, *diag;
+    double *snap_b, *snap_diag, *snap_p0, *b64;
+    double dt, rref, pref, gam, A, inv_V, inv_h, inv_h2;
+    const double *bc, *rm1;
+    struct Pts { T rn; };
+    __device__ void member(const Phys& ph, const DevState* d) {
+        this->NT = ph.NT;
+        dt = d->dt;
+        rref = d->rho_ref;
+        pref = d->p_ref;
+        gam = gamma_psi(ph);
+        A = ph.A;
+        inv_V = ph.inv_V;
+        inv_h = ph.inv_h;
+        inv_h2 = ph.inv_h2;
+        bc = ph.bdf2 ? d->bdf : nullptr;
+        rm1 = ph.rm1;
+    }
+    __device__ void init(double* acc) const { acc[0] = acc[1] = acc[2] = 0.0; }
+    __device__ Pts load(size_t P) const { return {stream_ld(rn + P)}; }
+    __device__ void cell(size_t P, const T (&v)[6][13], const T (&)[3], const T (&)[3], const Pts& p,
+                         double* acc) const {
+        T hl[3][5], pv[7], phf[3], dgT;
+#pragma unroll
+        for (int d = 0; d < 3; ++d) cross_line(v[2 + d], d, hl[d]);
+        cross7(v[5], pv);
+        double b;
+        corr_rhs_cell(v[0], v[1], hl, pv, p.rn, dt, rref, pref, gam, A, inv_V, inv_h, inv_h2, b, dgT,
+                      phf, bc, bc ? rm1[P] : 0.0);
+        double a3[3] = {acc[0], acc[1], acc[2]};
+        corr_rhs_store(P, this->NT, b, dgT, phf, pref + (double)pv[0], phiH, rvec, diag, snap_b,
+                       snap_diag, snap_p0, b64, a3);
+#pragma unroll
+        for (int c = 0; c < 3; ++c) acc[c] = a3[c];
+    }
+    __device__ void first(DevState* d) const {
+        d->pcg.it_stop = kIterInf;
+        d->pcg.converged = 0;
+        d->pcg.iters = 0;
+    }
+};
+
+// Launch of k_tiled (or, where TL has rows, k_flat) over the tiled launch TL;
+// returns its block count (the number of partials a reducing functor writes).
+template <typename T, class K>
+static unsigned flat_launch(const Launch& TL, hipStream_t s, const Phys& ph, const DevState* st,
+                            const K& k) {
+    Phys pt = ph;
+    pt.cz = TL.cz;
+    pt.nz = TL.nz;
+    const size_t rows = (size_t)K::NS * (TL.rows + 4) + (K::FACES ? 2 * TL.rows + 1 : 0);
+    hipLaunchKernelGGL((k_flat<T, K>), TL.grid, TL.block, rows * ph.n * sizeof(T), s, pt,
+                       const_cast<DevState*>(st), k);
+    return TL.nblocks;
+}
 template <typename T, class K>
 static unsigned tiled_launch(const Launch& TL, hipStream_t s, const Phys& ph, const DevState* st,
                              const K& k) {
+    if (TL.rows) return flat_launch<T>(TL, s, ph, st, k);
     Phys pt = ph;
     pt.cz = TL.cz;
     pt.nz = TL.nz;
@@ -3994,15 +4299,28 @@ Launch make_launch(int n, int batch) {
 
 Launch make_tiled_launch(int n, int batch, int cz_tile) {
     Launch L{};
-    if (n < 64 || n % kTX != 0 || n % kTY != 0) return L;   // nblocks = 0: not available
-    const int gx = n / kTX, gy = n / kTY;
-    int nz = kTiledBlocks / (gx * gy);
+    int gx = 1, gy, want, least;
+    if (n >= kFlatFieldMaxN && n % kTX == 0 && n % kTY == 0) {
+        gx = n / kTX;
+        gy = n / kTY;
+        want = kTiledBlocks;
+        least = 8;
+        L.block = dim3(kTX, kTY, 1);
+    } else {
+        const int rows = flat_field_rows(n);
+        if (!rows) return L;   // nblocks = 0: not available
+        gy = (n + rows - 1) / rows;
+        L.rows = (n + gy - 1) / gy;
+        want = kFlatFieldBlocks / batch;
+        least = 1;
+        L.block = dim3((L.rows * n + 63) / 64 * 64, 1, 1);
+    }
+    int nz = want / (gx * gy);
     nz = nz < 1 ? 1 : nz;
     int cz = (n + nz - 1) / nz;
-    if (cz < 8) cz = 8;
+    if (cz < least) cz = least;
     if (cz_tile > 0) cz = cz_tile < n ? cz_tile : n;
     nz = (n + cz - 1) / cz;
-    L.block = dim3(kTX, kTY, 1);
     L.grid = dim3(gx, gy, nz * batch);
     L.nblocks = L.grid.x * L.grid.y * L.grid.z;
     L.cz = cz;
@@ -4148,7 +4466,16 @@ template <typename T>
 void Ops<T>::mom_sweep(const Launch& L, const Launch& TL, hipStream_t s, const Phys& ph,
                        const DevState* st, const T* uin, T* uout, const T* phi, const T* aP,
                        const T* src, const T* pn) {
-    if (TL.nblocks) {
+    if (TL.rows) {
+        FlatMomSweep<T, false> k{};
+        for (int m = 0; m < 3; ++m) k.sf[m] = uin + m * ph.NT;
+        k.sf[3] = pn;
+        k.face = phi;
+        k.aP = aP;
+        k.s = src;
+        k.out = uout;
+        flat_launch<T>(TL, s, ph, st, k);
+    } else if (TL.nblocks) {
         Phys pt = ph;
         pt.cz = TL.cz;
         pt.nz = TL.nz;
@@ -4163,7 +4490,18 @@ template <typename T>
 void Ops<T>::hbya(const Launch& L, const Launch& TL, hipStream_t s, const Phys& ph,
                   const DevState* st, const T* uin, T* hb, const T* phi, const T* aP,
                   const T* src, const T* rk, T* w, T* p0) {
-    if (TL.nblocks) {
+    if (TL.rows) {
+        FlatMomSweep<T, true> k{};
+        for (int m = 0; m < 3; ++m) k.sf[m] = uin + m * ph.NT;
+        k.face = phi;
+        k.aP = aP;
+        k.s = src;
+        k.rk = rk;
+        k.out = hb;
+        k.w = w;
+        k.p0 = p0;
+        flat_launch<T>(TL, s, ph, st, k);
+    } else if (TL.nblocks) {
         Phys pt = ph;
         pt.cz = TL.cz;
         pt.nz = TL.nz;
@@ -4179,6 +4517,23 @@ unsigned Ops<T>::corr_rhs(const Launch& L, const Launch& TL, hipStream_t s, cons
                           DevState* st, const T* rn, const T* rk, const T* w, const T* hb,
                           const T* p0, T* phiH, T* r, T* diag, double* part_u, double* snap_b,
                           double* snap_diag, double* snap_p0, double* b64) {
+    if (TL.rows) {
+        FlatCorrRhs<T> k{};
+        k.sf[0] = w;
+        k.sf[1] = rk;
+        for (int d = 0; d < 3; ++d) k.sf[2 + d] = hb + d * ph.NT;
+        k.sf[5] = p0;
+        k.part = part_u;
+        k.rn = rn;
+        k.phiH = phiH;
+        k.rvec = r;
+        k.diag = diag;
+        k.snap_b = snap_b;
+        k.snap_diag = snap_diag;
+        k.snap_p0 = snap_p0;
+        k.b64 = b64;
+        return flat_launch<T>(TL, s, ph, st, k);
+    }
     if (TL.nblocks) {
         Phys pt = ph;
         pt.cz = TL.cz;

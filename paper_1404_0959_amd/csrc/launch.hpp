@@ -34,10 +34,23 @@ Launch make_launch(int n, int batch = 1);
 // thread along z (bx a power of two in 16..256, 1 <= cz <= n).
 Launch make_launch_shaped(int n, int batch, int bx, int cz);
 
-// Launch of the LDS-tiled z-marching kernels (64 x 8 threads per block); nblocks
-// is 0 when n is not a multiple of the tile (64 x 8); at n = 64 one tile spans
-// x and its x halo wraps onto itself.  Blocks march over at least 8 planes, or
-// exactly min(cz_tile, n) when cz_tile > 0 (a tuned choice).
+// Launch of the z-marching field kernels: on 64 x 8 tiles for n a multiple of 64
+// from 128 on, marching over at least 8 planes; else on flattened rows (rows
+// x-rows per block) where flat_field_rows allows; else nblocks is 0.  Blocks march
+// over exactly min(cz_tile, n) planes when cz_tile > 0 (a tuned choice).
+// Flattened rows: as many as fit 512 threads (256 registers a thread in FP64), at
+// least 4, so that the y halo is no larger than the block's own rows: n <= 128.
+// Below n = 40 the gathered kernels are as fast (the launch's latency is all).
+// z is cut for one block per CU over all members: a single grid of 70^3 takes
+// 3-plane marches, 16 members of 64^3 take whole columns (3-plane marches there
+// cost 18 % of a step, reading two halo planes for each of their own).  A
+// member's cells do not depend on the cut; sums over its blocks (mass, ||b||^2)
+// are then added in another order than a single grid's.
+constexpr int kFlatFieldRows = 4, kFlatFieldThreads = 512, kFlatFieldBlocks = 256;
+constexpr int kFlatFieldMinN = 40, kFlatFieldMaxN = kFlatFieldThreads / kFlatFieldRows;
+constexpr int flat_field_rows(int n) {
+    return n >= kFlatFieldMinN && n <= kFlatFieldMaxN ? kFlatFieldThreads / n : 0;
+}
 Launch make_tiled_launch(int n, int batch = 1, int cz_tile = 0);
 
 // Launch of the CG kernel for fields of elem_bytes per value.

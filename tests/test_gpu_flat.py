@@ -45,3 +45,69 @@ def test_cg_matches_oracle(P, ora, n):
         xg, it_g, _, st = P.helm_solve(d(psidt), d(w), d(b), x0=d(x0), tol=1e-14, maxit=maxit)
         assert st == P.WARN_NOT_CONVERGED and it_g == maxit
         assert np.max(np.abs(xg.cpu().numpy() - xo)) <= 1e-12 * np.max(np.abs(xo))
+
+
+def _fields(P, s, classes):
+    bits = P.FIELD_RHO | P.FIELD_U | P.FIELD_PHI | P.FIELD_P | (P.FIELD_RHO_P if classes else 0)
+    return {k: v.cpu().numpy() for k, v in s.fields(bits).items()}
+
+
+@pytest.mark.parametrize("precision,n,variant", [
+    ("fp64", 65, {}), ("fp64", 70, {}), ("fp64", 128 - 1, {}),
+    ("fp64", 70, dict(two_way=True, gravity=(0.1, 0.0, -1.0))),
+    ("fp64", 75, dict(bdf2=True)), ("fp64", 75, dict(mom_tol=1e-8)), ("fp64", 70, dict(fourier=True)),
+    ("fp32", 66, {}), ("fp32", 101, {}), ("fp32", 200, {}),
+    ("fp32", 70, dict(two_way=True, gravity=(0.1, 0.0, -1.0))),
+])
+def test_step_matches_gathered(P, monkeypatch, precision, n, variant):
+    """Two steps on the flat-row kernels against the gathered ones
+    (PISOC_UNTILED=1): both call the same cell arithmetic, so the CG iteration
+    counts and flags agree and the fields agree to rounding, with the bounds of the
+    tiled kernels' comparison (FP64: 1e-11 of the spread; FP32: 5e-5 of the spread
+    plus 16 FP32 ulps of the magnitude)."""
+    from paper_1404_0959_amd.inputs import make_hit_case
+    variant = dict(variant)
+    classes = 0 if variant.get("fourier") else 2
+    case = make_hit_case(n, 7, mach=0.5, stokes=(0.1, 0.4)[:classes])
+    if variant.pop("fourier", False):
+        variant["fourier"] = dict(R=1.0, cv=2.5, kappa=1e-3, T0=case.C)
+    kw = dict(p_tol=1e-9) if precision == "fp64" else dict(
+        p_tol=1e-6, precision=P.FP32_REFINED, inner_tol=1e-6)
+    runs = []
+    for untiled in (False, True):
+        if untiled:
+            monkeypatch.setenv("PISOC_UNTILED", "1")
+        s = P.Solver.from_case(case, **kw, **variant)
+        st, info = s.step(2)
+        assert st in (P.OK, P.WARN_DUST)
+        runs.append((_fields(P, s, classes), [(i["pcg_iters"], i["flags"], i["mom_iters"]) for i in info],
+                     [i["dt"] for i in info]))
+        monkeypatch.delenv("PISOC_UNTILED", raising=False)
+    (fa, ia, da), (fb, ib, db) = runs
+    assert ia == ib
+    np.testing.assert_allclose(da, db, rtol=1e-12 if precision == "fp64" else 1e-6)
+    tol, ulps = (1e-11, 0.0) if precision == "fp64" else (5e-5, 16 * np.finfo(np.float32).eps)
+    for k in fa:
+        spread = np.max(np.abs(fb[k] - fb[k].mean()))
+        bound = tol * spread + ulps * np.max(np.abs(fb[k]))
+        d = np.max(np.abs(fa[k] - fb[k]))
+        assert d <= bound, (k, d, bound)
+
+
+@pytest.mark.parametrize("n", [65, 70, 100])
+def test_chebyshev_matches_oracle(P, ora, n):
+    """The polynomial-preconditioned solve on flattened rows: the oracle's iteration
+    count, residual and solution, as for the other forms."""
+    import torch
+    rng = np.random.default_rng(400 + n)
+    h = 2 * math.pi / n
+    w = 0.01 * (1.0 + 0.2 * rng.random((n, n, n)))
+    psidt = 3.0 * 0.01 / h ** 2 * (1.0 + 0.2 * rng.random((n, n, n)))
+    b = rng.standard_normal((n, n, n))
+    xo, it_o, rel_o = ora.pcg_cheb(psidt, ora.kfaces(w), b, tol=1e-10, maxit=500)
+    d = lambda a: torch.as_tensor(a, device="cuda")
+    xg, it_g, rel_g, st = P.helm_solve(d(psidt), d(w), d(b), tol=1e-10, maxit=500,
+                                       precond=P.PRECOND_CHEB)
+    assert st == P.OK and it_g == it_o, (it_g, it_o)
+    assert abs(rel_g - rel_o) <= 1e-3 * rel_o
+    assert np.max(np.abs(xg.cpu().numpy() - xo)) <= 1e-12 * np.max(np.abs(xo))
