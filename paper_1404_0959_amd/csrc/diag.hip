@@ -1,6 +1,6 @@
 // diag.hip -- diagnostics of the velocity field on gfx950: the energy
-// spectrum and the Taylor micro-scale (through a radix-2 Stockham FFT done in
-// LDS, one line per LDS row), and the second invariant Q of the velocity
+// spectrum and the Taylor micro-scale (through a radix-4 Stockham FFT whose
+// lines cross LDS between stages), and the second invariant Q of the velocity
 // gradient.  These are the paper's validation quantities of the flow (Results
 // section: energy spectrum, Taylor micro-scale; third figure: Q iso-surfaces).
 //
@@ -13,12 +13,13 @@
 // s + 1/2, E(s) = sum over the shell of |u_hat|^2 / 2, so sum_s E(s) =
 // <|u|^2>/2.  Taylor micro-scale lambda = sqrt(5 sum E / D) with D = sum_k
 // |k|^2 |u_hat(k)|^2 / 2.  Every sum runs in a fixed order (bitwise
-// reproducible): per row of wavevectors, per plane, then over the planes.
+// reproducible).
 //
 // Also here: the plain streaming kernel that measures the practical HBM
 // ceiling of a given mix of reads and writes (no stencil, no reduction).
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <array>
 #include <cmath>
 #include <cstdint>
@@ -33,8 +34,25 @@ namespace {
 
 using cplx = double2;
 
-constexpr int kFftThreads = 256;
-constexpr int kFftLds = 1024;        // complex values per LDS buffer (two buffers)
+// ---- FFT ----
+// Radix-4 Stockham transforms (one radix-2 stage first when log2 n is odd) of
+// lines of n complex values, a block holding L lines in LDS, one radix-4
+// butterfly per thread and stage.  A stage with sub-transforms of size Ns takes
+// x[j + r n/4], r = 0..3, times exp(-2 pi i k r / (4 Ns)), k = j mod Ns, and leaves
+// its four outputs at 4 (j - k) + k + r Ns.  The first stage's inputs come
+// straight from global memory and the last one's outputs leave from registers,
+// so a line crosses LDS once per stage boundary.
+//
+// The input is real: the x pass transforms two rows as one complex line and
+// keeps the H = n/2 + 1 non-negative kx of each (f(-k) = conj f(k)); y and z
+// passes run on that half, the z pass bins |f|^2 without writing it back.  The
+// three components share every launch.  Bound: memory, 8 + 8 (x), 16 (y) and 8
+// bytes per cell and component (z) against 120 with full complex fields and
+// separate binning passes.  256^3, all components: 0.15 ms each for x and y (5.4
+// TB/s), 0.21 for z and the shells, in place of 3.2 together.
+constexpr int kFftItems = 512;       // butterflies per block and stage
+constexpr int kSpecBlocks = 768;     // blocks (partials) of the binning pass
+constexpr int kMaxBins2 = 2;         // shells per thread: at most 888 (n = 1024) over 512
 
 bool pow2(int n) { return n >= 8 && n <= 1024 && (n & (n - 1)) == 0; }
 int ilog2(int n) {
@@ -42,159 +60,328 @@ int ilog2(int n) {
     while ((1 << l) < n) ++l;
     return l;
 }
-// lines per FFT block: the two LDS buffers hold L lines of n complex values
-int fft_lines(int n) {
-    int L = kFftLds / n;
-    return L > n ? n : (L < 1 ? 1 : L);
-}
 
 // Shell of an integer |k|^2: s with s - 1/2 <= sqrt(k2) < s + 1/2, in integers
 // ((s + 1/2)^2 <= k2 <=> k2 >= s^2 + s + 1 for integer k2).
-__host__ __device__ inline int shell_of(int64_t k2) {
+inline int shell_of(int64_t k2) {
     int64_t s = (int64_t)sqrt((double)k2);
     while (s * s > k2) --s;
     while ((s + 1) * (s + 1) <= k2) ++s;
     return (int)(s + (k2 >= s * s + s + 1 ? 1 : 0));
 }
 
-// One FFT pass along axis AX (0 x, 1 y, 2 z) of the n^3 complex field f, in
-// place: block b loads L whole lines into LDS, runs log2(n) radix-2 Stockham
-// stages (stage with sub-transforms of size Ns: y[2(j - k) + k] = a + w b,
-// y[2(j - k) + k + Ns] = a - w b, a = x[j], b = x[j + n/2], k = j mod Ns,
-// w = exp(-i pi k / Ns)) and writes the lines back in natural order.  Along
-// x the lines are rows (contiguous); along y and z a block takes L lines at
-// consecutive x, so that each element's loads are L consecutive values.
-// With re (pass x only) the input is the real field re, imaginary part 0.
-template <int AX>
-__global__ void __launch_bounds__(kFftThreads) k_fft_axis(cplx* f, const double* re, int n,
-                                                         int logn, int L) {
-    extern __shared__ cplx lds_fft[];
-    cplx* A = lds_fft;
-    cplx* B = lds_fft + L * n;
-    cplx* W = lds_fft + 2 * L * n;   // twiddles exp(-2 pi i m / n), m < n/2
-    const int tid = threadIdx.x;
-    for (int m = tid; m < n / 2; m += kFftThreads) {
-        double sn, cs;
-        sincospi(-2.0 * (double)m / (double)n, &sn, &cs);
-        W[m] = {cs, sn};
-    }
-    const size_t nn = (size_t)n * n;
-    const int first = blockIdx.x * L;          // first line of the block
-    auto addr = [&](int l, int e) -> size_t {
-        if (AX == 0) {
-            const int idx = first + l, j = idx % n, k = idx / n;
-            return (size_t)e + (size_t)n * j + nn * k;
-        }
-        const int i0 = first % n, o = first / n;   // o: z (AX = 1) or y (AX = 2)
-        if (AX == 1) return (size_t)(i0 + l) + (size_t)n * e + nn * o;
-        return (size_t)(i0 + l) + (size_t)n * o + nn * e;
+// Pitch of a half row of n/2 + 1 values: whole 128-byte lines, so that the y and z
+// passes' tiles of 8 kx are lines.
+__host__ __device__ inline int half_pitch(int n) { return (n / 2 + 8) / 8 * 8; }
+// and of a plane: one line more than its rows, so that a z line's values do not
+// all lie a multiple of 32 KiB apart.
+__host__ __device__ inline size_t plane_pitch(int n) { return (size_t)n * half_pitch(n) + 8; }
+
+__device__ inline cplx cmul(cplx a, cplx b) { return {a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x}; }
+
+// tw[m] = exp(-2 pi i m / n)
+__global__ void k_fft_table(cplx* tw, int n) {
+    const int m = blockIdx.x * blockDim.x + threadIdx.x;
+    if (m >= n) return;
+    double sn, cs;
+    sincospi(-2.0 * (double)m / (double)n, &sn, &cs);
+    tw[m] = {cs, sn};
+}
+
+// The stages between the thread's inputs a (elements j + r n/4 of its line) and
+// its last butterfly's outputs, which stay in a: element base + r n/4 of the
+// line.  S(e) is the LDS slot of element e of the thread's line; act: the
+// thread has a line (every thread takes the barriers).
+template <class SLOT>
+__device__ inline int fft_stages(cplx (&a)[4], int n, int logn, int j, bool act, cplx* lds,
+                                 const cplx* W, SLOT&& S) {
+    const int q = n >> 2;
+    int Ns = 1;
+    auto exchange = [&](const int (&to)[4]) {
+        if (act)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) lds[S(to[r])] = a[r];
+        __syncthreads();
+        if (act)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) a[r] = lds[S(j + r * q)];
+        __syncthreads();
     };
-    for (int t = tid; t < L * n; t += kFftThreads) {
-        const int l = AX == 0 ? t / n : t % L;
-        const int e = AX == 0 ? t % n : t / L;
-        const size_t a = addr(l, e);
-        A[l * n + e] = re ? cplx{re[a], 0.0} : f[a];
+    if (logn & 1) {
+        const cplx s0 = {a[0].x + a[2].x, a[0].y + a[2].y}, d0 = {a[0].x - a[2].x, a[0].y - a[2].y};
+        const cplx s1 = {a[1].x + a[3].x, a[1].y + a[3].y}, d1 = {a[1].x - a[3].x, a[1].y - a[3].y};
+        a[0] = s0;
+        a[1] = d0;
+        a[2] = s1;
+        a[3] = d1;
+        exchange({2 * j, 2 * j + 1, 2 * (j + q), 2 * (j + q) + 1});
+        Ns = 2;
+    }
+    for (;;) {
+        const int k = j & (Ns - 1);
+        if (Ns > 1) {
+            const int st = k * (q / Ns);   // exp(-2 pi i k r / (4 Ns)) = W[r k n / (4 Ns)]
+#pragma unroll
+            for (int r = 1; r < 4; ++r) a[r] = cmul(a[r], W[r * st]);
+        }
+        const cplx b0 = {a[0].x + a[2].x, a[0].y + a[2].y}, b1 = {a[0].x - a[2].x, a[0].y - a[2].y};
+        const cplx b2 = {a[1].x + a[3].x, a[1].y + a[3].y};
+        const cplx b3 = {a[1].y - a[3].y, a[3].x - a[1].x};   // -i (a1 - a3)
+        a[0] = {b0.x + b2.x, b0.y + b2.y};
+        a[1] = {b1.x + b3.x, b1.y + b3.y};
+        a[2] = {b0.x - b2.x, b0.y - b2.y};
+        a[3] = {b1.x - b3.x, b1.y - b3.y};
+        const int base = 4 * (j - k) + k;
+        if (4 * Ns == n) return base;
+        exchange({base, base + Ns, base + 2 * Ns, base + 3 * Ns});
+        Ns *= 4;
+    }
+}
+
+// x pass: row pairs 2 p, 2 p + 1 of component blockIdx.y as one complex line;
+// with Z the line's transform the rows' are (Z(k) + conj Z(-k)) / 2 and
+// (Z(k) - conj Z(-k)) / (2 i).
+__global__ void __launch_bounds__(kFftItems) k_fft_x(const double* __restrict__ u, cplx* __restrict__ f,
+                                                     const cplx* __restrict__ tw, int n, int logn, int L) {
+    extern __shared__ cplx lds_fft[];
+    cplx* const W = lds_fft + (size_t)L * n;
+    const int tid = threadIdx.x, q = n >> 2, H = n / 2 + 1, Hp = half_pitch(n);
+    const size_t nn = (size_t)n * n, N = nn * n;
+    for (int m = tid; m < n; m += blockDim.x) W[m] = tw[m];
+    __syncthreads();
+    const int l = tid / q, j = tid & (q - 1);
+    const bool act = l < L;
+    const double* r0 = u + blockIdx.y * N + (size_t)(blockIdx.x * L + (act ? l : 0)) * 2 * n;
+    cplx a[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) a[r] = {r0[j + r * q], r0[n + j + r * q]};
+    auto S = [&](int e) { return l * n + e; };
+    const int base = fft_stages(a, n, logn, j, act, lds_fft, W, S);
+    if (act)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) lds_fft[S(base + r * q)] = a[r];
+    __syncthreads();
+    const int row0 = blockIdx.x * L * 2;   // first row within the component
+    for (int t = tid; t < L * 2 * H; t += blockDim.x) {
+        const int row = t / H, k = t - row * H;
+        const cplx* Z = lds_fft + (row >> 1) * n;
+        const cplx zp = Z[k], zm = Z[(n - k) & (n - 1)];
+        const int z = (row0 + row) / n, y = (row0 + row) - z * n;   // n a power of two
+        f[(blockIdx.y * n + z) * plane_pitch(n) + (size_t)y * Hp + k] = row & 1 ? cplx{0.5 * (zp.y + zm.y), 0.5 * (zm.x - zp.x)}
+                         : cplx{0.5 * (zp.x + zm.x), 0.5 * (zp.y - zm.y)};
+    }
+}
+
+// y pass in place: L lines at consecutive kx (the last tile of a row may hold
+// fewer) of one plane of one component.
+__global__ void __launch_bounds__(kFftItems) k_fft_y(cplx* __restrict__ f, const cplx* __restrict__ tw,
+                                                     int n, int logn, int L) {
+    extern __shared__ cplx lds_fft[];
+    cplx* const W = lds_fft + (size_t)L * n;
+    const int tid = threadIdx.x, q = n >> 2, H = n / 2 + 1, Hp = half_pitch(n);
+    for (int m = tid; m < n; m += blockDim.x) W[m] = tw[m];
+    __syncthreads();
+    const int l = tid % L, j = tid / L, kx = blockIdx.x * L + l;
+    const bool act = j < q && kx < H;
+    cplx* line = f + blockIdx.y * plane_pitch(n) + (act ? kx : 0);   // blockIdx.y: plane of a component
+    cplx a[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) a[r] = line[(size_t)(act ? j + r * q : 0) * Hp];
+    const int base = fft_stages(a, n, logn, j, act, lds_fft, W, [&](int e) { return e * L + l; });
+    if (act)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) line[(size_t)(base + r * q) * Hp] = a[r];
+}
+
+// floor(sqrt(v)) for 0 <= v <= 3 512^2: the hardware root is within 1 ulp (6e-5
+// below 1024), and the roots of r^2 - 1 and r^2 lie 1 / (2 r) >= 5.6e-4 apart.
+__device__ inline int isqrt(int v) { return (int)(__builtin_amdgcn_sqrtf((float)v) + 1.5e-4f); }
+
+// z pass and binning: tiles of L lines at consecutive kx and one ky, dealt to the
+// blocks in turn.  The lines' energies e = |f|^2 / (2 n^6), twice for the kx whose
+// conjugate half is not stored, go to LDS, line by line; then the threads sum the
+// shells: on a line, shell s holds the |kz| with s^2 - s + 1 <= k^2 <= s^2 + s, a
+// run of them.  G = threads / shells groups share the lines (one thread per
+// shell left half the block idle), their sums are added at the end; each runs
+// over tiles, lines and |kz| in a fixed order.  part[block][0 / 1][s]: E(s), and
+// the shell's sum of |k|^2 e.
+__global__ void __launch_bounds__(kFftItems) k_fft_z_bins(const cplx* __restrict__ f,
+                                                          const cplx* __restrict__ tw, int n, int logn,
+                                                          int L, int bins, double inv_n6,
+                                                          double* __restrict__ part) {
+    extern __shared__ cplx lds_fft[];
+    cplx* const W = lds_fft + (size_t)L * n;
+    double* const en = reinterpret_cast<double*>(lds_fft);
+    const int tid = threadIdx.x, nthr = blockDim.x, q = n >> 2, H = n / 2 + 1, Hp = half_pitch(n);
+    for (int m = tid; m < n; m += nthr) W[m] = tw[m];
+    const int l = tid % L, j = tid / L;
+    const int tx = (H + L - 1) / L, tiles = 3 * n * tx;
+    const int G = nthr / bins > 1 ? nthr / bins : 1;
+    const int grp = G > 1 ? tid / bins : 0, s0 = G > 1 ? tid - grp * bins : tid;
+    double E[kMaxBins2] = {}, D[kMaxBins2] = {};
+    // a tile's inputs, loaded while the last tile's shells are summed
+    const size_t pp = plane_pitch(n);
+    cplx a[4];
+    auto load = [&](int t) {
+        const int kx = (t % tx) * L + l, ky = (t / tx) % n, c = t / (tx * n);
+        const bool act = j < q && kx < H;
+        const cplx* line = f + (size_t)c * n * pp + (size_t)ky * Hp + (act ? kx : 0);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) a[r] = line[(size_t)(act ? j + r * q : 0) * pp];
+    };
+    if ((int)blockIdx.x < tiles) load(blockIdx.x);
+    for (int t = blockIdx.x; t < tiles; t += gridDim.x) {
+        const int x0 = (t % tx) * L, ky = (t / tx) % n, kx = x0 + l;
+        const bool act = j < q && kx < H;
+        __syncthreads();   // the last tile's energies are summed (and W is there)
+        const int base = fft_stages(a, n, logn, j, act, lds_fft, W, [&](int e) { return e * L + l; });
+        const double w = (kx == 0 || kx == n / 2 ? 0.5 : 1.0) * inv_n6;
+        if (act)
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+                en[l * (n + 1) + base + r * q] = w * (a[r].x * a[r].x + a[r].y * a[r].y);
+        if (t + (int)gridDim.x < tiles) load(t + gridDim.x);
+        lds_barrier();
+        const int kys = ky < n / 2 ? ky : n - ky, lines = H - x0 < L ? H - x0 : L;
+#pragma unroll
+        for (int i = 0; i < kMaxBins2; ++i) {
+            const int s = s0 + i * nthr;
+            if (s >= bins || grp >= G) break;
+            const int top = s * s + s, bot = s == 0 ? 0 : s * s - s + 1;
+            for (int y = grp; y < lines; y += G) {
+                const int kxy = (x0 + y) * (x0 + y) + kys * kys;
+                if (top < kxy) break;   // kxy grows with y
+                const int hi = isqrt(top - kxy), lo = bot <= kxy ? 0 : isqrt(bot - kxy - 1) + 1;
+                const int end = hi < n / 2 ? hi : n / 2;
+                const double* e0 = en + y * (n + 1);
+                for (int m = lo; m <= end; ++m) {
+                    // kz = m and -m, one and the same at 0 and n / 2
+                    const double e = (m == 0 || m == n / 2 ? 0.5 : 1.0) * (e0[m] + e0[(n - m) & (n - 1)]);
+                    E[i] += e;
+                    D[i] += (double)(kxy + m * m) * e;
+                }
+            }
+        }
+    }
+    // the groups' sums, in group order
+    __syncthreads();
+    if (G > 1 && grp < G) {
+        en[(grp * bins + s0) * 2] = E[0];
+        en[(grp * bins + s0) * 2 + 1] = D[0];
     }
     __syncthreads();
-    const int half = n >> 1;
-    for (int s = 0, Ns = 1; s < logn; ++s, Ns <<= 1) {
-        for (int t = tid; t < L * half; t += kFftThreads) {
-            const int l = t / half, j = t - l * half;
-            const int k = j & (Ns - 1);
-            // exp(-i pi k / Ns) = exp(-2 pi i (k n / (2 Ns)) / n)
-            const cplx tw = W[k * (half / Ns)];
-            const double cs = tw.x, sn = tw.y;
-            const cplx a = A[l * n + j], x = A[l * n + j + half];
-            const cplx wb = {x.x * cs - x.y * sn, x.x * sn + x.y * cs};
-            const int base = l * n + 2 * (j - k) + k;
-            B[base] = {a.x + wb.x, a.y + wb.y};
-            B[base + Ns] = {a.x - wb.x, a.y - wb.y};
-        }
-        __syncthreads();
-        cplx* t = A;
-        A = B;
-        B = t;
+    if (grp != 0) return;
+    for (int g = 1; g < G; ++g) {
+        E[0] += en[(g * bins + s0) * 2];
+        D[0] += en[(g * bins + s0) * 2 + 1];
     }
-    for (int t = tid; t < L * n; t += kFftThreads) {
-        const int l = AX == 0 ? t / n : t % L;
-        const int e = AX == 0 ? t % n : t / L;
-        f[addr(l, e)] = A[l * n + e];
+    double* out = part + (size_t)blockIdx.x * 2 * bins;
+#pragma unroll
+    for (int i = 0; i < kMaxBins2; ++i) {
+        const int s = s0 + i * nthr;
+        if (s >= bins) break;
+        out[s] = E[i];
+        out[bins + s] = D[i];
     }
 }
 
-// Signed wavenumber of DFT index i (components in [-n/2, n/2)).
-__device__ inline int wavenumber(int i, int n) { return i < n / 2 ? i : i - n; }
-
-// Shell binning of one component's transform f, in three fixed-order passes.
-// 1. One thread per x-row of wavevectors (fixed ky, kz): walking kx in order of
-//    |kx| (0, 1, -1, 2, -2, ..., -n/2) the shell index never decreases, so the
-//    row's energies e = |f|^2 / (2 n^6) sum into runs, one per shell, written to
-//    rowpart[row][s - s0] with s0 the shell of kx = 0 (W = n/2 + 2 entries per
-//    row hold every shell the row reaches; shells it skips stay 0); rowd[row]
-//    receives the row's sum of |k|^2 e.
-__global__ void __launch_bounds__(kFftThreads) k_spectrum_rows(const cplx* f, int n, int W,
-                                                             double inv_n6, double* rowpart,
-                                                             double* rowd) {
-    const size_t row = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (row >= (size_t)n * n) return;
-    const int ky = wavenumber((int)(row % n), n), kz = wavenumber((int)(row / n), n);
-    const int64_t kyz = (int64_t)ky * ky + (int64_t)kz * kz;
-    const int s0 = shell_of(kyz);
-    double* out = rowpart + row * (size_t)W;
-    for (int t = 0; t < W; ++t) out[t] = 0.0;
-    const cplx* line = f + row * (size_t)n;
-    int cur = s0;
-    double acc = 0.0, dk = 0.0;
-    for (int m = 0; m < n; ++m) {
-        const int kx = m == 0 ? 0 : m == n - 1 ? -n / 2 : (m & 1) ? (m + 1) / 2 : -(m / 2);
-        const cplx v = line[kx >= 0 ? kx : kx + n];
-        const double e = 0.5 * (v.x * v.x + v.y * v.y) * inv_n6;
-        const int64_t k2 = kyz + (int64_t)kx * kx;
-        const int sh = shell_of(k2);
-        if (sh != cur) {
-            out[cur - s0] = acc;
-            acc = 0.0;
-            cur = sh;
-        }
-        acc += e;
-        dk += (double)k2 * e;
-    }
-    out[cur - s0] = acc;
-    rowd[row] = dk;
+// Totals over the blocks, in 16 slices added in order.
+__global__ void __launch_bounds__(1024) k_spectrum_total(const double* __restrict__ part, int nb,
+                                                         int count, double* __restrict__ out) {
+    __shared__ double lds[16][64];
+    const int ex = threadIdx.x & 63, sl = threadIdx.x >> 6;
+    const int e = blockIdx.x * 64 + ex;
+    const int per = (nb + 15) / 16, b0 = sl * per, b1 = b0 + per < nb ? b0 + per : nb;
+    double s = 0.0;
+    if (e < count)
+#pragma unroll 8
+        for (int b = b0; b < b1; ++b) s += part[(size_t)b * count + e];
+    lds[sl][ex] = s;
+    __syncthreads();
+    if (sl != 0 || e >= count) return;
+    s = lds[0][ex];
+#pragma unroll
+    for (int r = 1; r < 16; ++r) s += lds[r][ex];
+    out[e] = s;
 }
 
-// 2. Per plane kz and shell s: the sum over the plane's rows in row order
-//    (s = bins: the rows' |k|^2 e sums) into plane[kz * (bins + 1) + s].
-__global__ void __launch_bounds__(64) k_spectrum_planes(const double* rowpart, const double* rowd,
-                                                        int n, int W, int bins, double* plane) {
-    const int s = blockIdx.x * blockDim.x + threadIdx.x;
-    const int zi = blockIdx.y;
-    if (s > bins) return;
-    const int kz = wavenumber(zi, n);
-    double acc = 0.0;
-    for (int j = 0; j < n; ++j) {
-        const size_t row = (size_t)j + (size_t)n * zi;
-        if (s == bins) {
-            acc += rowd[row];
-            continue;
-        }
-        const int ky = wavenumber(j, n);
-        const int t = s - shell_of((int64_t)ky * ky + (int64_t)kz * kz);
-        if (t >= 0 && t < W) acc += rowpart[row * (size_t)W + t];
-    }
-    plane[(size_t)zi * (bins + 1) + s] = acc;
+// ---- stencil diagnostics ----
+// z-marches over 64 x 8 columns of cells, any n: a block stages each plane of its
+// column with a halo of H cells in LDS (positions wrapped, so that a column past
+// the grid's edge holds the periodic images and its threads only skip their
+// outputs), the next plane's loads in flight meanwhile; what the z direction
+// needs waits in register queues.  Before, every cell gathered its stencils
+// through the caches: 39 loads for Q, 81 for the filter, whose nine filtered
+// fields then went through memory.  256^3: Q 0.17 ms instead of 0.52 (3.1 TB/s of
+// its four words), the filtered statistics 0.48 instead of 1.55.  Bound: staging,
+// barrier and arithmetic in turn, with two to three blocks per CU to overlap them.
+constexpr int kMX = 64, kMY = 8, kMThreads = kMX * kMY, kMBlocks = 1024;
+constexpr int kSY = 4;   // rows of the kernels that keep a ring of planes
+struct March {
+    dim3 grid;
+    int cz;
+    unsigned blocks;
+};
+March make_march(int n, int rows = kMY) {
+    March m;
+    const int gx = (n + kMX - 1) / kMX, gy = (n + rows - 1) / rows;
+    int nz = kMBlocks * (kMY / rows) / (gx * gy);
+    nz = nz < 1 ? 1 : nz;
+    m.cz = std::max((n + nz - 1) / nz, std::min(n, 4));
+    nz = (n + m.cz - 1) / m.cz;
+    m.grid = dim3(gx, gy, nz);
+    m.blocks = (unsigned)gx * gy * nz;
+    return m;
 }
 
-// 3. Totals over the planes (in plane order) and over the three components'
-//    plane sets (in component order): out[s] = E(s), out[bins] = D.
-__global__ void __launch_bounds__(kFftThreads) k_spectrum_total(const double* part, int nblk,
-                                                              int bins, double* out) {
-    const size_t set = (size_t)nblk * (bins + 1);
-    for (int s = threadIdx.x; s <= bins; s += kFftThreads) {
-        double acc = 0.0;
-        for (int c = 0; c < 3; ++c)
-            for (int b = 0; b < nblk; ++b) acc += part[c * set + (size_t)b * (bins + 1) + s];
-        out[s] = acc;
+// One plane of NF fields with a halo of H cells around 64 x RY: staged values in
+// flight and where they go.
+template <int NF, int H, int RY = kMY>
+struct Stage {
+    static constexpr int kW = kMX + 2 * H, kR = RY + 2 * H, kCells = kW * kR, kThreads = kMX * RY;
+    static constexpr int kPer = (kCells + kThreads - 1) / kThreads;
+    size_t src[kPer];
+    double v[NF][kPer];
+    __device__ void init(int n, int i0, int j0, int tid) {
+#pragma unroll
+        for (int q = 0; q < kPer; ++q) {
+            const int c = tid + q * kThreads, y = c / kW, x = c - y * kW;
+            const int gx = (i0 - H + x + n) % n, gy = (j0 - H + y + n) % n;   // n >= 8 > H
+            src[q] = c < kCells ? (size_t)gx + (size_t)n * gy : 0;
+        }
+    }
+    __device__ void load(const double* f, size_t N, size_t plane) {
+#pragma unroll
+        for (int m = 0; m < NF; ++m)
+#pragma unroll
+            for (int q = 0; q < kPer; ++q) v[m][q] = f[m * N + plane + src[q]];
+    }
+    __device__ void store(double* lds, int tid) const {
+#pragma unroll
+        for (int q = 0; q < kPer; ++q) {
+            const int c = tid + q * kThreads;
+            if (c < kCells)
+#pragma unroll
+                for (int m = 0; m < NF; ++m) lds[m * kCells + c] = v[m][q];
+        }
+    }
+};
+
+// Gauss-I4 derivative (I4(q)_{P+1/2} - I4(q)_{P-1/2}) / h from the cells -2..2.
+__device__ inline double dgauss5(double a, double b, double c, double d, double e, double inv_h) {
+    return ((9.0 * (c + d) - (b + e)) * 0.0625 - (9.0 * (b + c) - (a + d)) * 0.0625) * inv_h;
+}
+
+// The gradient of three fields on the plane two behind the last one staged: its
+// x and y neighbours from the plane's ring slot p (the three fields C apart, rows
+// W apart), its z neighbours from the queue c.
+__device__ inline void march_grad(const double* p, int W, int C, const double (&c)[3][5], double inv_h,
+                                  double (&G)[3][3]) {
+#pragma unroll
+    for (int m = 0; m < 3; ++m, p += C) {
+        G[m][0] = dgauss5(p[-2], p[-1], c[m][2], p[1], p[2], inv_h);
+        G[m][1] = dgauss5(p[-2 * W], p[-W], c[m][2], p[W], p[2 * W], inv_h);
+        G[m][2] = dgauss5(c[m][0], c[m][1], c[m][2], c[m][3], c[m][4], inv_h);
     }
 }
 
@@ -202,31 +389,50 @@ __global__ void __launch_bounds__(kFftThreads) k_spectrum_total(const double* pa
 // derivative d_j q = (I4(q)_{P+1/2 e_j} - I4(q)_{P-1/2 e_j}) / h; partial sums
 // of Q and of (d_i u_i)^2 (the discrete identity sum Q = -(1/2) sum (div u)^2
 // holds for these antisymmetric, commuting difference operators).
-__global__ void __launch_bounds__(kBlock) k_qcrit(int n, double inv_h, const double* __restrict__ u,
-                                                  double* __restrict__ q, double* part) {
-    const size_t N = (size_t)n * n * n;
-    double v[2] = {0.0, 0.0};
-    for (size_t P = (size_t)blockIdx.x * blockDim.x + threadIdx.x; P < N;
-         P += (size_t)gridDim.x * blockDim.x) {
-        const int i = (int)(P % n), j = (int)((P / n) % n), k = (int)(P / ((size_t)n * n));
-        const CellIdx c(n, i, j, k, 0);
-        double G[3][3];
+__global__ void __launch_bounds__(kMX * kSY) k_qcrit(int n, int cz, double inv_h,
+                                                     const double* __restrict__ u,
+                                                     double* __restrict__ q, double* part) {
+    typedef Stage<3, 2, kSY> St;
+    constexpr int W = St::kW, C = St::kCells;
+    __shared__ double lds[3 * 3 * C];   // a ring of three planes
+    const BlockXYZ bp = block_xyz();
+    const int tx = threadIdx.x, ty = threadIdx.y, tid = tx + kMX * ty;
+    const int i0 = bp.x * kMX, j0 = bp.y * kSY, k0 = bp.z * cz, k1 = k0 + cz < n ? k0 + cz : n;
+    const size_t nn = (size_t)n * n, N = nn * n;
+    const bool act = i0 + tx < n && j0 + ty < n;
+    const size_t col = act ? (size_t)(i0 + tx) + (size_t)n * (j0 + ty) : 0;
+    const int at = (ty + 2) * W + tx + 2;
+    St st;
+    st.init(n, i0, j0, tid);
+    double c[3][5] = {}, v[2] = {0.0, 0.0};
+    auto plane = [&](int k) { return nn * (size_t)((k + n) % n); };
+    st.load(u, N, plane(k0 - 2));
+    int slot = 0;
+    for (int k = k0 - 2; k < k1 + 2; ++k, slot = slot == 2 ? 0 : slot + 1) {
+        double* const pk = lds + slot * 3 * C;
+        st.store(pk, tid);
+        st.load(u, N, plane(k + 1 < k1 + 2 ? k + 1 : k));
+        lds_barrier();
 #pragma unroll
-        for (int a = 0; a < 3; ++a) {
-            double g[13];
-            gather13(u + a * N, c, g);
+        for (int m = 0; m < 3; ++m) {
 #pragma unroll
-            for (int b = 0; b < 3; ++b) G[a][b] = dgauss13(g, b, inv_h);
+            for (int t = 0; t < 4; ++t) c[m][t] = c[m][t + 1];
+            c[m][4] = pk[m * C + at];
         }
-        double Q = 0.0;
+        if (k >= k0 + 2 && act) {
+            double G[3][3];   // of plane k - 2, whose ring slot is the next one
+            march_grad(lds + (slot == 2 ? 0 : slot + 1) * 3 * C + at, W, C, c, inv_h, G);
+            double Q = 0.0;
 #pragma unroll
-        for (int a = 0; a < 3; ++a)
+            for (int a = 0; a < 3; ++a)
 #pragma unroll
-            for (int b = 0; b < 3; ++b) Q -= 0.5 * G[a][b] * G[b][a];
-        q[P] = Q;
-        const double div = G[0][0] + G[1][1] + G[2][2];
-        v[0] += Q;
-        v[1] += div * div;
+                for (int b = 0; b < 3; ++b) Q -= 0.5 * G[a][b] * G[b][a];
+            const double div = G[0][0] + G[1][1] + G[2][2];
+            stream_st(q + (col + nn * (size_t)(k - 2)), Q);
+            v[0] += Q;
+            v[1] += div * div;
+        }
+        lds_barrier();
     }
     block_partials<2, 0u>(v, part);
 }
@@ -241,76 +447,148 @@ __global__ void __launch_bounds__(kBlock) k_qcrit_total(const double* part, unsi
     }
 }
 
-// Filtered (a-priori sub-grid) statistics: the separable top-hat of width 2h
-// (weights 1/4, 1/2, 1/4 along each axis) of u_i and of u_i u_j, into nine
-// fields F (u_bar x, y, z; bar(u u) xx, xy, xz, yy, yz, zz).
-__global__ void __launch_bounds__(kBlock) k_sgs_filter(int n, const double* __restrict__ u,
-                                                       double* __restrict__ F) {
-    const size_t N = (size_t)n * n * n;
-    for (size_t P = (size_t)blockIdx.x * blockDim.x + threadIdx.x; P < N;
-         P += (size_t)gridDim.x * blockDim.x) {
-        const int i = (int)(P % n), j = (int)((P / n) % n), k = (int)(P / ((size_t)n * n));
-        const CellIdx c(n, i, j, k, 0);
-        double acc[9] = {0, 0, 0, 0, 0, 0, 0, 0, 0};
-        for (int dz = -1; dz <= 1; ++dz)
-            for (int dy = -1; dy <= 1; ++dy)
-                for (int dx = -1; dx <= 1; ++dx) {
-                    const double w = (dx ? 0.25 : 0.5) * (dy ? 0.25 : 0.5) * (dz ? 0.25 : 0.5);
-                    const size_t Q = c.self() + (size_t)(ptrdiff_t)(c.off[0][dx + 2] +
-                                                                    c.off[1][dy + 2] +
-                                                                    c.off[2][dz + 2]);
-                    const double a = u[Q], b = u[N + Q], e = u[2 * N + Q];
-                    acc[0] += w * a;
-                    acc[1] += w * b;
-                    acc[2] += w * e;
-                    acc[3] += w * a * a;
-                    acc[4] += w * a * b;
-                    acc[5] += w * a * e;
-                    acc[6] += w * b * b;
-                    acc[7] += w * b * e;
-                    acc[8] += w * e * e;
-                }
+// The separable top-hat of width 2h (weights 1/4, 1/2, 1/4 along each axis) over
+// the staged plane's x and y, around the cell at `at`.
+template <class F>
+__device__ inline double tophat_xy(int W, F&& f) {
+    double r[3];
 #pragma unroll
-        for (int f = 0; f < 9; ++f) F[f * N + P] = acc[f];
+    for (int y = -1; y <= 1; ++y)
+        r[y + 1] = 0.25 * (f(y * W - 1) + f(y * W + 1)) + 0.5 * f(y * W);
+    return 0.25 * (r[0] + r[2]) + 0.5 * r[1];
+}
+
+// Filtered (a-priori sub-grid) statistics, first pass: u_bar.
+__global__ void __launch_bounds__(kMThreads) k_sgs_filter(int n, int cz, const double* __restrict__ u,
+                                                          double* __restrict__ ub) {
+    typedef Stage<3, 1> St;
+    __shared__ double lds[3 * St::kCells];
+    const BlockXYZ bp = block_xyz();
+    const int tx = threadIdx.x, ty = threadIdx.y, tid = tx + kMX * ty;
+    const int i0 = bp.x * kMX, j0 = bp.y * kMY, k0 = bp.z * cz, k1 = k0 + cz < n ? k0 + cz : n;
+    const size_t nn = (size_t)n * n, N = nn * n;
+    const bool act = i0 + tx < n && j0 + ty < n;
+    const size_t col = act ? (size_t)(i0 + tx) + (size_t)n * (j0 + ty) : 0;
+    const int at = (ty + 1) * St::kW + tx + 1;
+    St st;
+    st.init(n, i0, j0, tid);
+    double f[3][3];
+    auto plane = [&](int k) { return nn * (size_t)((k + n) % n); };
+    st.load(u, N, plane(k0 - 1));
+    for (int k = k0 - 1; k < k1 + 1; ++k) {
+        st.store(lds, tid);
+        st.load(u, N, plane(k + 1 < k1 + 1 ? k + 1 : k));
+        lds_barrier();
+#pragma unroll
+        for (int m = 0; m < 3; ++m) {
+            const double* p = lds + m * St::kCells + at;
+            f[m][0] = f[m][1];
+            f[m][1] = f[m][2];
+            f[m][2] = tophat_xy(St::kW, [&](int o) { return p[o]; });
+        }
+        lds_barrier();
+        if (k < k0 + 1 || !act) continue;
+#pragma unroll
+        for (int m = 0; m < 3; ++m)
+            ub[m * N + col + nn * (size_t)(k - 1)] = 0.25 * (f[m][0] + f[m][2]) + 0.5 * f[m][1];
     }
 }
 
-// Per cell tau_ij = bar(u_i u_j) - u_bar_i u_bar_j, k_sgs = tau_ii / 2,
+// Second pass, per cell: bar(u_i u_j) filtered on the fly,
+// tau_ij = bar(u_i u_j) - u_bar_i u_bar_j, k_sgs = tau_ii / 2,
 // S_bar_ij = (d_j u_bar_i + d_i u_bar_j) / 2 (Gauss-I4), Pi = -tau_ij S_bar_ij;
 // partial sums of |u_bar|^2 / 2, k_sgs, Pi and of the cells with Pi < 0.
-__global__ void __launch_bounds__(kBlock) k_sgs_stats(int n, double inv_h,
-                                                      const double* __restrict__ F,
-                                                      double* part) {
-    const size_t N = (size_t)n * n * n;
+// Columns of 64 x 4 cells, a ring of three u_bar planes in LDS and running sums of
+// the products' z filter keep the registers at 164: with the derivatives of
+// three planes and the products of three in registers (250 of them) one block of
+// 64 x 8 had a CU to itself, 395 us at 256^3 against 309.
+__global__ void __launch_bounds__(kMX * kSY) k_sgs_stats(int n, int cz, double inv_h,
+                                                         const double* __restrict__ u,
+                                                         const double* __restrict__ ub, double* part) {
+    typedef Stage<3, 1, kSY> Su;
+    typedef Stage<3, 2, kSY> Sb;
+    constexpr int W = Sb::kW, C = Sb::kCells;
+    __shared__ double lds[3 * Su::kCells + 3 * 3 * C];
+    double* const ldsb = lds + 3 * Su::kCells;
+    const BlockXYZ bp = block_xyz();
+    const int tx = threadIdx.x, ty = threadIdx.y, tid = tx + kMX * ty;
+    const int i0 = bp.x * kMX, j0 = bp.y * kSY, k0 = bp.z * cz, k1 = k0 + cz < n ? k0 + cz : n;
+    const size_t nn = (size_t)n * n, N = nn * n;
+    const bool act = i0 + tx < n && j0 + ty < n;
+    const int au = (ty + 1) * Su::kW + tx + 1, ab = (ty + 2) * W + tx + 2;
+    Su su;
+    Sb sb;
+    su.init(n, i0, j0, tid);
+    sb.init(n, i0, j0, tid);
+    // bar(u u) in the order xx, xy, xz, yy, yz, zz: with P(k) the plane's x-y
+    // filtered product, f[0] = P(k - 1) / 4 + P(k) / 2 and f[1] = P(k) / 4 of the
+    // last plane k staged
+    constexpr int kA[6] = {0, 0, 0, 1, 1, 2}, kB[6] = {0, 1, 2, 1, 2, 2};
+    double f[6][2] = {}, c[3][5] = {};
     double v[4] = {0.0, 0.0, 0.0, 0.0};
-    for (size_t P = (size_t)blockIdx.x * blockDim.x + threadIdx.x; P < N;
-         P += (size_t)gridDim.x * blockDim.x) {
-        const int i = (int)(P % n), j = (int)((P / n) % n), k = (int)(P / ((size_t)n * n));
-        const CellIdx c(n, i, j, k, 0);
-        double G[3][3], ub[3];
+    auto plane = [&](int k) { return nn * (size_t)((k + n) % n); };
+    // step k stages u_bar's plane k and u's plane k - 1; the output plane is k - 2
+    su.load(u, N, plane(k0 - 3));
+    sb.load(ub, N, plane(k0 - 2));
+    int slot = 0;
+    for (int k = k0 - 2; k < k1 + 2; ++k, slot = slot == 2 ? 0 : slot + 1) {
+        double* const pb = ldsb + slot * 3 * C;
+        su.store(lds, tid);
+        sb.store(pb, tid);
+        const int kn = k + 1 < k1 + 2 ? k + 1 : k;
+        su.load(u, N, plane(kn - 1));
+        sb.load(ub, N, plane(kn));
+        lds_barrier();
+        double bar[6];
 #pragma unroll
-        for (int a = 0; a < 3; ++a) {
-            double g[13];
-            gather13(F + a * N, c, g);
-            ub[a] = g[0];
+        for (int e = 0; e < 6; ++e) bar[e] = f[e][0];
 #pragma unroll
-            for (int b = 0; b < 3; ++b) G[a][b] = dgauss13(g, b, inv_h);
-        }
-        // bar(u u) in the order xx, xy, xz, yy, yz, zz
-        const int slot[3][3] = {{3, 4, 5}, {4, 6, 7}, {5, 7, 8}};
-        double ks = 0.0, pi = 0.0;
+        for (int y = -1; y <= 1; ++y) {
+            double a[3][3];
 #pragma unroll
-        for (int a = 0; a < 3; ++a)
+            for (int m = 0; m < 3; ++m)
 #pragma unroll
-            for (int b = 0; b < 3; ++b) {
-                const double tau = F[slot[a][b] * N + P] - ub[a] * ub[b];
-                if (a == b) ks += 0.5 * tau;
-                pi -= tau * 0.5 * (G[a][b] + G[b][a]);
+                for (int x = 0; x < 3; ++x) a[m][x] = lds[m * Su::kCells + au + y * Su::kW + x - 1];
+            const double wy = y == 0 ? 0.5 : 0.25;
+#pragma unroll
+            for (int e = 0; e < 6; ++e) {
+                const double r = wy * (0.25 * (a[kA[e]][0] * a[kB[e]][0] + a[kA[e]][2] * a[kB[e]][2]) +
+                                       0.5 * (a[kA[e]][1] * a[kB[e]][1]));
+                if (y == -1) f[e][0] = r;   // the plane's P, in turn
+                else f[e][0] += r;
             }
-        v[0] += 0.5 * (ub[0] * ub[0] + ub[1] * ub[1] + ub[2] * ub[2]);
-        v[1] += ks;
-        v[2] += pi;
-        v[3] += pi < 0.0 ? 1.0 : 0.0;
+        }
+#pragma unroll
+        for (int e = 0; e < 6; ++e) {
+            const double P = f[e][0];
+            bar[e] += 0.25 * P;
+            f[e][0] = f[e][1] + 0.5 * P;
+            f[e][1] = 0.25 * P;
+        }
+#pragma unroll
+        for (int m = 0; m < 3; ++m) {
+#pragma unroll
+            for (int t = 0; t < 4; ++t) c[m][t] = c[m][t + 1];
+            c[m][4] = pb[m * C + ab];
+        }
+        if (k >= k0 + 2 && act) {
+            // the output plane's x and y derivatives: its ring slot is the next one
+            double G[3][3];
+            march_grad(ldsb + (slot == 2 ? 0 : slot + 1) * 3 * C + ab, W, C, c, inv_h, G);
+            double ks = 0.0, pi = 0.0;
+#pragma unroll
+            for (int e = 0; e < 6; ++e) {
+                const int a = kA[e], b = kB[e];
+                const double tau = bar[e] - c[a][2] * c[b][2];
+                if (a == b) ks += 0.5 * tau;
+                pi -= (a == b ? 1.0 : 2.0) * tau * 0.5 * (G[a][b] + G[b][a]);
+            }
+            v[0] += 0.5 * (c[0][2] * c[0][2] + c[1][2] * c[1][2] + c[2][2] * c[2][2]);
+            v[1] += ks;
+            v[2] += pi;
+            v[3] += pi < 0.0 ? 1.0 : 0.0;
+        }
+        lds_barrier();
     }
     block_partials<4, 0u>(v, part);
 }
@@ -323,17 +601,18 @@ __global__ void __launch_bounds__(kBlock) k_sgs_total(const double* part, unsign
         for (int c = 0; c < 4; ++c) out[c] = t[c];
 }
 
-constexpr unsigned kQBlocks = 2048;
+constexpr unsigned kMaxMarch = 4096;   // blocks of a march: n = 1024 has 16 x 256 columns of 4 rows
 
 size_t align256(size_t x) { return (x + 255) / 256 * 256; }
 
-// Workspace: complex field, per-component plane partials, totals.
+// Workspace: the spectrum's half-complex fields or u_bar (never both at once),
+// twiddles, binning partials and totals, the stencil kernels' partials.
 struct DiagLayout {
-    size_t field, part, total_out, qpart, bytes;
+    size_t field, tw, part, total_out, qpart, bytes;
 };
 DiagLayout diag_layout(int n) {
     DiagLayout d{};
-    const size_t N = (size_t)n * n * n;
+    const size_t nn = (size_t)n * n;
     const int bins = shell_of(3LL * (n / 2) * (n / 2)) + 1;
     size_t off = 0;
     auto take = [&](size_t b) {
@@ -341,12 +620,11 @@ DiagLayout diag_layout(int n) {
         off = align256(off + b);
         return o;
     };
-    // the spectrum's complex field or the nine filtered fields (never both at once)
-    // (the spectrum's row sums follow its complex field inside the same region)
-    d.field = take(sizeof(double) * 9 * N);
-    d.part = take(sizeof(double) * 3 * (size_t)n * (bins + 1));
-    d.total_out = take(sizeof(double) * (bins + 1));
-    d.qpart = take(sizeof(double) * (4 * kQBlocks + 16));
+    d.field = take(std::max(sizeof(cplx) * 3 * n * plane_pitch(n), sizeof(double) * 3 * nn * n));
+    d.tw = take(sizeof(cplx) * n);
+    d.part = take(sizeof(double) * 2 * (size_t)kSpecBlocks * bins);
+    d.total_out = take(sizeof(double) * 2 * bins);
+    d.qpart = take(sizeof(double) * (4 * kMaxMarch + 16));
     d.bytes = off;
     return d;
 }
@@ -419,45 +697,44 @@ pisoc_status pisoc_diag_spectrum(int32_t n, const double* d_u, double* h_E, int3
     hipStream_t s = reinterpret_cast<hipStream_t>(hip_stream);
     char* ws = reinterpret_cast<char*>(d_ws);
     cplx* f = reinterpret_cast<cplx*>(ws + Ly.field);
+    cplx* tw = reinterpret_cast<cplx*>(ws + Ly.tw);
     double* part = reinterpret_cast<double*>(ws + Ly.part);
     double* tot = reinterpret_cast<double*>(ws + Ly.total_out);
     const size_t N = (size_t)n * n * n;
-    const int L = fft_lines(n), logn = ilog2(n);
-    const unsigned blocks = (unsigned)((size_t)n * n / L);
-    const size_t lds = sizeof(cplx) * (2 * (size_t)L * n + n / 2);
+    const int logn = ilog2(n), q = n / 4, H = n / 2 + 1;
     const double inv_n6 = 1.0 / ((double)N * (double)N);
-    const int W = n / 2 + 2;
-    double* rowpart = reinterpret_cast<double*>(ws + Ly.field + sizeof(cplx) * N);
-    double* rowd = rowpart + (size_t)n * n * W;
-    const size_t set = (size_t)n * (nbins + 1);
-    const unsigned rowblocks = (unsigned)(((size_t)n * n + kFftThreads - 1) / kFftThreads);
-    for (int c = 0; c < 3; ++c) {
-        hipLaunchKernelGGL(k_fft_axis<0>, dim3(blocks), dim3(kFftThreads), lds, s, f, d_u + c * N,
-                           n, logn, L);
-        hipLaunchKernelGGL(k_fft_axis<1>, dim3(blocks), dim3(kFftThreads), lds, s, f, nullptr, n,
-                           logn, L);
-        hipLaunchKernelGGL(k_fft_axis<2>, dim3(blocks), dim3(kFftThreads), lds, s, f, nullptr, n,
-                           logn, L);
-        hipLaunchKernelGGL(k_spectrum_rows, dim3(rowblocks), dim3(kFftThreads), 0, s, f, n, W,
-                           inv_n6, rowpart, rowd);
-        hipLaunchKernelGGL(k_spectrum_planes, dim3((nbins + 64) / 64, n), dim3(64), 0, s, rowpart,
-                           rowd, n, W, nbins, part + c * set);
+    // lines per block: of the x pass (row pairs, a power of two), of the others
+    // (consecutive kx, the H of them in tiles of nearly equal width)
+    const int Lx = std::min(kFftItems / q, n * n / 2);
+    const int Lmax = kFftItems / q;
+    int tx = (H + Lmax - 1) / Lmax, L = (H + tx - 1) / tx;
+    if (Lmax >= 8) {   // whole 128-byte lines
+        L = (L + 7) / 8 * 8;
+        tx = (H + L - 1) / L;
     }
-    hipLaunchKernelGGL(k_spectrum_total, dim3(1), dim3(kFftThreads), 0, s, part, n, nbins, tot);
+    const dim3 bx((Lx * q + 63) / 64 * 64), b((L * q + 63) / 64 * 64);
+    const size_t ldsx = sizeof(cplx) * ((size_t)Lx * n + n), lds = sizeof(cplx) * ((size_t)L * n + n);
+    const int nb = std::min(kSpecBlocks, 3 * n * tx);
+    hipLaunchKernelGGL(k_fft_table, dim3((n + 255) / 256), dim3(256), 0, s, tw, n);
+    hipLaunchKernelGGL(k_fft_x, dim3(n * n / 2 / Lx, 3), bx, ldsx, s, d_u, f, tw, n, logn, Lx);
+    hipLaunchKernelGGL(k_fft_y, dim3(tx, 3 * n), b, lds, s, f, tw, n, logn, L);
+    hipLaunchKernelGGL(k_fft_z_bins, dim3(nb), b, lds, s, f, tw, n, logn, L, nbins, inv_n6, part);
+    hipLaunchKernelGGL(k_spectrum_total, dim3((2 * nbins + 63) / 64), dim3(1024), 0, s, part, nb,
+                       2 * nbins, tot);
     if (hipGetLastError() != hipSuccess) return PISOC_ERR_HIP;
     // the totals come back through pageable memory after the stream has drained
     if (hipStreamSynchronize(s) != hipSuccess) return PISOC_ERR_HIP;
-    double* host = new (std::nothrow) double[nbins + 1];
+    double* host = new (std::nothrow) double[2 * nbins];
     if (!host) return PISOC_ERR_INVALID;
-    const bool ok = hipMemcpy(host, tot, sizeof(double) * (nbins + 1), hipMemcpyDeviceToHost) ==
+    const bool ok = hipMemcpy(host, tot, sizeof(double) * 2 * nbins, hipMemcpyDeviceToHost) ==
                     hipSuccess;
     if (ok) {
-        double e = 0.0;
-        for (int b = 0; b < nbins; ++b) {
-            h_E[b] = host[b];
-            e += host[b];
+        double e = 0.0, D = 0.0;
+        for (int b2 = 0; b2 < nbins; ++b2) {
+            h_E[b2] = host[b2];
+            e += host[b2];
+            D += host[nbins + b2];
         }
-        const double D = host[nbins];
         if (h_taylor) *h_taylor = D > 0.0 ? std::sqrt(5.0 * e / D) : 0.0;
         if (h_dsum) *h_dsum = D;
     }
@@ -473,12 +750,13 @@ pisoc_status pisoc_diag_qcrit(int32_t n, const double* d_u, double* d_q, double*
         return PISOC_ERR_WORKSPACE;
     const size_t N = (size_t)n * n * n;
     double* qpart = reinterpret_cast<double*>(reinterpret_cast<char*>(d_ws) + Ly.qpart);
-    double* out = qpart + 2 * kQBlocks;
+    double* out = qpart + 2 * kMaxMarch;
     hipStream_t s = reinterpret_cast<hipStream_t>(hip_stream);
     const double inv_h = (double)n / 6.283185307179586476925286766559;
-    hipLaunchKernelGGL(k_qcrit, dim3(kQBlocks), dim3(kBlock), 0, s, n, inv_h, d_u, d_q, qpart);
+    const March m = make_march(n, kSY);
+    hipLaunchKernelGGL(k_qcrit, m.grid, dim3(kMX, kSY), 0, s, n, m.cz, inv_h, d_u, d_q, qpart);
     if (!h_means) return hipGetLastError() == hipSuccess ? PISOC_OK : PISOC_ERR_HIP;
-    hipLaunchKernelGGL(k_qcrit_total, dim3(1), dim3(kBlock), 0, s, qpart, kQBlocks, out);
+    hipLaunchKernelGGL(k_qcrit_total, dim3(1), dim3(kBlock), 0, s, qpart, m.blocks, out);
     if (hipGetLastError() != hipSuccess || hipStreamSynchronize(s) != hipSuccess)
         return PISOC_ERR_HIP;
     double t[2];
@@ -496,14 +774,16 @@ pisoc_status pisoc_diag_sgs(int32_t n, const double* d_u, double* h_out, void* d
         return PISOC_ERR_WORKSPACE;
     const size_t N = (size_t)n * n * n;
     char* ws = reinterpret_cast<char*>(d_ws);
-    double* F = reinterpret_cast<double*>(ws + Ly.field);
+    double* ub = reinterpret_cast<double*>(ws + Ly.field);
     double* part = reinterpret_cast<double*>(ws + Ly.qpart);
-    double* out = part + 4 * kQBlocks;
+    double* out = part + 4 * kMaxMarch;
     hipStream_t s = reinterpret_cast<hipStream_t>(hip_stream);
     const double inv_h = (double)n / 6.283185307179586476925286766559;
-    hipLaunchKernelGGL(k_sgs_filter, dim3(kQBlocks), dim3(kBlock), 0, s, n, d_u, F);
-    hipLaunchKernelGGL(k_sgs_stats, dim3(kQBlocks), dim3(kBlock), 0, s, n, inv_h, F, part);
-    hipLaunchKernelGGL(k_sgs_total, dim3(1), dim3(kBlock), 0, s, part, kQBlocks, out);
+    const March m = make_march(n);
+    hipLaunchKernelGGL(k_sgs_filter, m.grid, dim3(kMX, kMY), 0, s, n, m.cz, d_u, ub);
+    const March ms = make_march(n, kSY);
+    hipLaunchKernelGGL(k_sgs_stats, ms.grid, dim3(kMX, kSY), 0, s, n, ms.cz, inv_h, d_u, ub, part);
+    hipLaunchKernelGGL(k_sgs_total, dim3(1), dim3(kBlock), 0, s, part, ms.blocks, out);
     if (hipGetLastError() != hipSuccess || hipStreamSynchronize(s) != hipSuccess)
         return PISOC_ERR_HIP;
     double t[4];
