@@ -1643,6 +1643,8 @@ __global__ void __launch_bounds__(64 * kRowWaves) k_pcg_spmv_rows(
 // that few threads carry both.  Threads past the last row repeat the block's
 // first cell and store nothing.  The z neighbours come from register queues;
 // loads past the chunk's last needed plane are clamped to planes already read.
+// Partial sums go out per sub planes, the march of a single grid: a batch whose
+// blocks march further adds a member's in the order of a run of its own.
 // Bound: latency.  At 32^3 a launch is the chain state and partials -> totals
 // -> p -> barrier -> q -> totals, at 70^3 the march over 2-3 planes; only from
 // 128^3 on does it come near the fabric's rate.  us per iteration, launch gap
@@ -1651,13 +1653,13 @@ __global__ void __launch_bounds__(64 * kRowWaves) k_pcg_spmv_rows(
 // 9.1, 17), 100^3 23.6 against 46 (13.0, 26.6), 160^3 84 against 89 (31.5,
 // 51), 192^3 130 against 140 (64 x 16 tiles; 58.5, 58.9), 250^3 263 against 538
 // (123, 248).
-template <typename T, int XM, int HW, int MT>
+template <typename T, int XM, int HW, int MT, bool SUBS>
 __global__ void __launch_bounds__(MT, 4) k_pcg_spmv_flat(
     Phys ph, DevState* st, int k, const T* __restrict__ rin, T* __restrict__ rout,
     const T* __restrict__ diag, const T* __restrict__ w, const T* __restrict__ pold,
     const T* __restrict__ pold2, T* __restrict__ pnew, const T* __restrict__ qold,
     T* __restrict__ q, T* __restrict__ x, const double* part_in, unsigned nb_in, double* part_out,
-    int fresh, int maxit, int xzero) {
+    int fresh, int maxit, int xzero, int sub, int per, int chunks) {
     constexpr bool UPD = XM > 0, XE = XM == 2;
     MEMBER(ph)
     extern __shared__ __align__(16) unsigned char flat_lds[];
@@ -1738,6 +1740,15 @@ __global__ void __launch_bounds__(MT, 4) k_pcg_spmv_flat(
     T pc = dirf(zc, oc);
     T kzm = (T(9) * (wm1 + w0) - (wmm + wp1)) * T(0.0625);
     double acc[CG_COLS] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+    // partials: one slot per row block and chunk of sub planes (per = cz / sub of
+    // them in a march, chunks in a column)
+    unsigned slot = bp_.y + gridDim.y * (unsigned)(mem_ * chunks + bz_ * per);
+    auto total = [&] {
+        __shared__ double red[kMaxWaves * CG_COLS];
+        const double t = block_reduce<CG_COLS, 0u, true>(acc, red, block_waves());
+        if (tid < CG_COLS) part_out[(size_t)tid * (gridDim.y * chunks * ph.batch) + slot] = t;
+    };
+    int kend = k0 + sub;
     for (int kk = k0; kk < k1; ++kk) {
         const T wp2 = wp2n;
         const T rp = resf(rnx, qnx);
@@ -1813,8 +1824,15 @@ __global__ void __launch_bounds__(MT, 4) k_pcg_spmv_flat(
             xc = xn1;
             o2c = o2n1;
         }
+        if (SUBS && kk + 1 == kend && kend < k1) {
+            total();
+#pragma unroll
+            for (int c = 0; c < CG_COLS; ++c) acc[c] = 0.0;
+            slot += gridDim.y;
+            kend += sub;
+        }
     }
-    block_partials<CG_COLS, 0u, true>(acc, part_out);
+    total();
 }
 
 // ---- CG preconditioned by a Chebyshev polynomial (stand-alone solve) ----
@@ -4340,7 +4358,8 @@ Launch make_spmv_launch(int n, int batch, int elem_bytes, int cz_tile) {
         L.block = dim3(64, kRowWaves, 1);
         L.grid = dim3(1, gy, nz * batch);
         L.nblocks = L.grid.x * L.grid.y * L.grid.z;
-        L.cz = cz;
+        L.cz = L.sub = cz;
+        L.nparts = L.nblocks;
         L.nz = nz;
         L.v = n / (64 * rh);
         L.h = rh;
@@ -4360,7 +4379,8 @@ Launch make_spmv_launch(int n, int batch, int elem_bytes, int cz_tile) {
         L.block = dim3(kTX, kTY, 1);
         L.grid = dim3(gx, gy, nz * batch);
         L.nblocks = L.grid.x * L.grid.y * L.grid.z;
-        L.cz = cz;
+        L.cz = L.sub = cz;
+        L.nparts = L.nblocks;
         L.nz = nz;
         return L;
     }
@@ -4375,6 +4395,13 @@ Launch make_spmv_launch(int n, int batch, int elem_bytes, int cz_tile) {
     nz = (n + cz - 1) / cz;
     L.rows = rows;
     L.block = dim3((rows * n + 63) / 64 * 64, 1, 1);
+    L.sub = cz;
+    L.nparts = gy * nz * batch;
+    if (batch > 1) {   // longer marches, whole chunks of the single grid's
+        const int most = std::max(1, kFlatBatchBlocks / (gy * batch));
+        cz *= (nz + most - 1) / most;
+        nz = (n + cz - 1) / cz;
+    }
     L.grid = dim3(1, gy, nz * batch);
     L.nblocks = L.grid.y * L.grid.z;
     L.cz = cz;
@@ -4599,15 +4626,20 @@ static void spmv_launch(const Launch& L, const Launch& TL, hipStream_t s, const 
         pt.nz = TL.nz;
         const size_t lds = flat_cg_lds(ph.n, TL.rows, sizeof(T));
         const bool one = 4u * ph.n <= TL.block.x;
-#define FLAT(HW, MT) \
-    hipLaunchKernelGGL((k_pcg_spmv_flat<T, XM, HW, MT>), TL.grid, TL.block, lds, s, pt, SPMV_ARGS)
-        if (TL.block.x <= 512) {
-            if (one) FLAT(1, 512);
-            else FLAT(2, 512);
-        } else {
-            if (one) FLAT(1, 1024);
-            else FLAT(2, 1024);
-        }
+#define FLAT(HW, MT, SUBS)                                                                         \
+    hipLaunchKernelGGL((k_pcg_spmv_flat<T, XM, HW, MT, SUBS>), TL.grid, TL.block, lds, s, pt,      \
+                       SPMV_ARGS, TL.sub, TL.cz / TL.sub, (ph.n + TL.sub - 1) / TL.sub)
+        auto run = [&](auto subs) {
+            if (TL.block.x <= 512) {
+                if (one) FLAT(1, 512, subs.value);
+                else FLAT(2, 512, subs.value);
+            } else {
+                if (one) FLAT(1, 1024, subs.value);
+                else FLAT(2, 1024, subs.value);
+            }
+        };
+        if (TL.sub < TL.cz) run(std::true_type{});
+        else run(std::false_type{});
 #undef FLAT
         return;
     }

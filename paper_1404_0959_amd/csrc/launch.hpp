@@ -19,6 +19,8 @@ struct Launch {
     int v = 0;          // CG kernel: cells per lane along x of the full-row form (0: tiles)
     int h = 0;          // and wavefronts per x-row
     int rows = 0;       // and x-rows per block of its flat form (0: another form)
+    int sub = 0;        // and planes per partial sum of a block (cz, or a divisor of it)
+    unsigned nparts = 0;   // and partial sums per column, all members
     bool nt = false;    // and its once-read fields streamed past the caches (make_spmv_launch)
 };
 
@@ -66,8 +68,8 @@ Launch make_tiled_launch(int n, int batch = 1, int cz_tile = 0);
 //   leave it a y halo as large as the tile; at 192 and below it is the faster.
 // * Every other n with flat_rows(n) >= 2: the flat form, rows x-rows per block.
 // nblocks is 0 when none is available.  Tiles march over at least 8 planes, or
-// like the flat form over exactly min(cz_tile, n) when cz_tile > 0 (a tuned
-// choice; the full-row form ignores it).
+// like the flat form's single grids over exactly min(cz_tile, n) when cz_tile > 0
+// (a tuned choice; the full-row form ignores it).
 // nt (full-row form): the fields a CG iteration reads once (r, q, p_old of the
 // main rows) are loaded non-temporally, so that w and diag, which every
 // iteration of a solve reads again, stay in the memory-side cache (kMallBytes)
@@ -85,9 +87,16 @@ constexpr int kFlatBeforeTiles = 256;
 // another to end and the launch's head totals few partials: of the shapes
 // swept at 24 sizes from 16 to 336 in both precisions the rule's is within
 // 10 % of the fastest, and half or twice as many blocks take 5-40 % longer.
+// A batch has blocks enough without short marches, and with the single grid's
+// most of a block's time is its head and halo planes: its blocks march over
+// several chunks, for at most kFlatBatchBlocks in all (the partial sums stay per
+// chunk, so a member's are those of a run of its own).  FP32, 12 members of 32^3
+// with 6 of 48^3 and 6 of 64^3: a step of all took 3.46 ms with the single
+// grid's marches, 3.20 so; a quarter, half or twice as many blocks 3.41, 3.30 and
+// 3.40, and 2 members of 64^3 are the same either way.
 // The block's LDS (two plane sets of R + 4 rows of w and R + 2 of p) stays
 // within kFlatLds beside the reduction's.
-constexpr int kFlatBlocks = 256;
+constexpr int kFlatBlocks = 256, kFlatBatchBlocks = 1024;
 constexpr size_t kFlatLds = 60 * 1024;
 constexpr size_t flat_cg_lds(int n, int rows, int elem_bytes) {
     return (size_t)2 * (2 * rows + 6) * n * elem_bytes;

@@ -211,9 +211,9 @@ Layout make_layout(const pisoc_params* p, int batch) {
     const size_t N = (size_t)p->n * p->n * p->n * (size_t)batch;
     const size_t es = p->precision == PISOC_FP64 ? sizeof(double) : sizeof(float);
     unsigned mb = std::max({make_launch(p->n, batch).nblocks, make_tiled_launch(p->n, batch).nblocks,
-                            make_spmv_launch(p->n, batch, (int)es).nblocks});
+                            make_spmv_launch(p->n, batch, (int)es).nparts});
     for (int c : {8, 16, 32}) {   // the chunks the autotuner may choose
-        mb = std::max(mb, make_spmv_launch(p->n, batch, (int)es, c).nblocks);
+        mb = std::max(mb, make_spmv_launch(p->n, batch, (int)es, c).nparts);
         mb = std::max(mb, make_tiled_launch(p->n, batch, c).nblocks);
     }
     for (auto [bx, cz] : shape_candidates(p->n))
@@ -487,7 +487,7 @@ pisoc_status run_pcg(pisoc_ctx* ctx, const CgVecs<T>& v, bool fresh, int iters, 
                      int* iters_max, bool xzero, unsigned nb_first, int cap = 0) {
     using O = Ops<T>;
     const int maxit = cap > 0 ? std::min(cap, ctx->prm.p_maxit) : ctx->prm.p_maxit;
-    const unsigned nb_cg = ctx->TS.nblocks ? ctx->TS.nblocks : ctx->L.nblocks;
+    const unsigned nb_cg = ctx->TS.nblocks ? ctx->TS.nparts : ctx->L.nblocks;
     auto launch = [&](int k) {
         CgArgs<T> a;
         a.rin = v.r[k == 0 ? 0 : (k + 1) & 1];
@@ -1788,7 +1788,7 @@ std::vector<int> chunk_candidates(int n, int d0) {
     return out;
 }
 std::vector<int> cg_chunk_candidates(const pisoc_ctx* ctx) {
-    return chunk_candidates(ctx->prm.n, make_spmv_launch(ctx->prm.n, ctx->batch, (int)ctx->es).cz);
+    return chunk_candidates(ctx->prm.n, make_spmv_launch(ctx->prm.n, ctx->batch, (int)ctx->es).sub);
 }
 
 // The same for the tiled field kernels' launch.
@@ -2575,7 +2575,7 @@ pisoc_status pisoc_ens_class_info(const pisoc_ens* e, int32_t cls, pisoc_ens_cla
     for (int c = 0; c < ctx->prm.n_corr; ++c)
         if (ctx->prm.guess != PISOC_GUESS_ZERO && (!audit_on(ctx) || ctx->audit.use[c]))
             o.guess_mask |= 1 << c;
-    o.cg_cells_z = ctx->TS.nblocks ? ctx->TS.cz : 0;
+    o.cg_cells_z = ctx->TS.nblocks ? ctx->TS.sub : 0;
     o.tiled_cells_z = ctx->TL.nblocks ? ctx->TL.cz : 0;
     *h_out = o;
     return PISOC_OK;
@@ -2619,7 +2619,7 @@ static Layout helm_layout(int32_t n) {
     Layout L{};
     const size_t N = (size_t)n * n * n;
     L.max_blocks = std::max({make_launch(n, 1).nblocks, make_tiled_launch(n, 1).nblocks,
-                             make_spmv_launch(n, 1, 8).nblocks});
+                             make_spmv_launch(n, 1, 8).nparts});
     size_t off = 0;
     auto take = [&](size_t bytes) { size_t o = off; off = align_up(off + bytes); return o; };
     L.state = take(sizeof(DevState));

@@ -111,3 +111,30 @@ def test_chebyshev_matches_oracle(P, ora, n):
     assert st == P.OK and it_g == it_o, (it_g, it_o)
     assert abs(rel_g - rel_o) <= 1e-3 * rel_o
     assert np.max(np.abs(xg.cpu().numpy() - xo)) <= 1e-12 * np.max(np.abs(xo))
+
+
+@pytest.mark.parametrize("precision,n,members", [
+    ("fp64", 20, 16), ("fp64", 33, 6), ("fp32", 66, 8), ("fp64", 66, 9),
+])
+def test_batched_cg_sums_as_a_single_run(P, precision, n, members):
+    """A batch's CG blocks march over several of the single grid's z-chunks (with a
+    short last march at 33 and 66) and total each chunk by itself: a member's
+    solves and fields are bitwise those of a run of its own."""
+    from paper_1404_0959_amd.inputs import make_hit_case
+    cs = [make_hit_case(n, 50 + m, mach=0.2 if m % 2 else 0.5, stokes=(0.1,)) for m in range(members)]
+    kw = dict(precision=P.FP32_REFINED if precision == "fp32" else P.FP64, p_tol=1e-7,
+              inner_tol=1e-5, cfl=0.5)
+    ens = P.Ensemble(cs, **kw)
+    st, infos = ens.step(2, mode=P.ENS_EAGER)
+    assert st in (P.OK, P.WARN_DUST)
+    for m in (0, members - 1):
+        s = P.Solver.from_case(cs[m], **kw)
+        st, rec = s.step(2)
+        assert st in (P.OK, P.WARN_DUST)
+        assert infos[m]["pcg_iters"] == rec[-1]["pcg_iters"]
+        a = {k: v.cpu().numpy() for k, v in ens.fields(m, P.FIELD_U | P.FIELD_P).items()}
+        b = {k: v.cpu().numpy() for k, v in s.fields(P.FIELD_U | P.FIELD_P).items()}
+        for k in a:
+            assert np.array_equal(a[k], b[k]), (m, k)
+        s.close()
+    ens.close()
