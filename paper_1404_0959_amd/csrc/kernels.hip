@@ -3260,8 +3260,11 @@ __global__ void __launch_bounds__(kTX * kTY) k_tiled(Phys ph, DevState* st, K ke
 // and now: momentum sweep 24.1 and 13.8 at 70^3, 42.7 and 28.9 at 100^3; a step's
 // field kernels in all 382 and 247, 700 and 511 (FP32 237 and 202, 378 and 369);
 // at 64^3, where the tiles' 8-plane minimum left 64 blocks, an FP64 step took 662
-// us on tiles and takes 476.
-template <typename T, class K>
+// us on tiles and takes 476.  Segments, us per whole step, gathered and now: FP64
+// 136^3 2577 and 2001, 160^3 3806 and 2768, 200^3 7790 and 5223, FP32 1397 and 1390,
+// 1859 and 1779, 4499 and 3812 (per cell the 64 x 8 tiles' 192^3 step takes 2 % less
+// than the one of 200^3).
+template <typename T, class K, bool SEG>
 __global__ void __launch_bounds__(kFlatFieldThreads) k_flat(Phys ph, DevState* st, K kern) {
     MEMBER(ph)
     extern __shared__ __align__(16) unsigned char flat_lds[];
@@ -3270,10 +3273,17 @@ __global__ void __launch_bounds__(kFlatFieldThreads) k_flat(Phys ph, DevState* s
     constexpr int NRA = K::NR > 0 ? K::NR : 1;
     constexpr unsigned XS = K::XS, YS = K::YS, ZS = K::ZS;
     constexpr int NY = __builtin_popcount(YS & ((1u << NS) - 1u));
+    constexpr int NX = __builtin_popcount(XS & ((1u << NS) - 1u));
+    constexpr int F1 = FACES ? 1 : 0;
     // halo cells per row of n: 4 per field read along y, 1 of the y faces; a
     // block has at least kFlatFieldRows rows
     constexpr int kPer = (4 * NY + (FACES ? 1 : 0) + kFlatFieldRows - 1) / kFlatFieldRows;
     constexpr int kPerA = kPer > 0 ? kPer : 1;
+    // a segment's block (at least kSegRows rows of kSegWidth cells) has no more
+    // halo cells per thread, the x halo's 4 per row and field included
+    static_assert(!SEG || (4 * NY + F1) * kSegWidth + (4 * NX + F1) * kSegRows <=
+                              kPerA * kSegRows * kSegWidth, "halo cells of a segment");
+    constexpr int kHalo = SEG ? kPerA : kPer;
     const size_t N = ncell(ph);
     K k = kern;
     k.member(ph, st + mem_);
@@ -3284,6 +3294,10 @@ __global__ void __launch_bounds__(kFlatFieldThreads) k_flat(Phys ph, DevState* s
     const int R = (n + (int)gridDim.y - 1) / (int)gridDim.y;
     const int j0 = bp_.y * R;
     const int rows = n - j0 < R ? n - j0 : R;
+    // columns i0 .. i0 + wd - 1 of the rows, in LDS from ox0 on with row pitch pw
+    const int W = SEG ? seg_width(n, (int)gridDim.x) : n, i0 = SEG ? bp_.x * W : 0;
+    const int wd = SEG && n - i0 < W ? n - i0 : W;
+    const int ox0 = SEG ? 2 : 0, pw = SEG ? W + 4 : n;
     const int k0 = bz_ * cz;
     const int k1 = k0 + cz < n ? k0 + cz : n;
     const size_t nn = (size_t)n * n;
@@ -3292,25 +3306,26 @@ __global__ void __launch_bounds__(kFlatFieldThreads) k_flat(Phys ph, DevState* s
     // LDS: R + 4 rows of each stencil field, the x faces' R rows, the y faces'
     // R + 1 rows (from y = j0 - 1 on)
     T* const U = reinterpret_cast<T*>(flat_lds);
-    const int us = (R + 4) * n;
+    const int us = (R + 4) * pw;
     T* const FX = U + NS * us;
-    T* const FY = FX + R * n;
-    const bool act = tid < rows * n;
-    const int y = act ? tid / n : 0, xi = act ? tid - y * n : 0;
-    const size_t col = base_ + (size_t)n * (j0 + y) + xi;
-    const int ow = (y + 2) * n;
-    const int xm1 = wr(xi - 1), xm2 = wr(xi - 2), xp1 = wr(xi + 1), xp2 = wr(xi + 2);
+    T* const FY = FX + R * pw;
+    const bool act = tid < rows * wd;
+    const int y = act ? tid / wd : 0, xc = act ? tid - y * wd : 0, xi = ox0 + xc;
+    const size_t col = base_ + (size_t)n * (j0 + y) + i0 + xc;
+    const int ow = (y + 2) * pw;
+    auto wx = [&](int a) { return SEG ? a : wr(a); };
+    const int xm1 = wx(xi - 1), xm2 = wx(xi - 2), xp1 = wx(xi + 1), xp2 = wx(xi + 2);
     typedef const T __attribute__((address_space(1)))* gptr;   // global memory
     gptr hsrc[kPerA];
     size_t hoff[kPerA];
     int hdst[kPerA];
 #pragma unroll
-    for (int q = 0; q < kPer; ++q) {
+    for (int q = 0; q < kHalo; ++q) {
         const int jb = tid + q * B;
         hsrc[q] = (gptr)k.sf[0];
         hoff[q] = col;
         hdst[q] = -1;
-        const int h = jb / n, hx = jb - h * n;      // halo row h of the job list
+        const int h = jb / wd, hx = jb - h * wd;    // halo row h of the job list
         int f = -1, at = 0;                         // its field
 #pragma unroll
         for (int g = 0; g < NS; ++g)
@@ -3323,12 +3338,36 @@ __global__ void __launch_bounds__(kFlatFieldThreads) k_flat(Phys ph, DevState* s
             }
         if (f >= 0) {                               // rows j0-2, j0-1, j0+rows, j0+rows+1
             const int r4 = h & 3, yy = r4 < 2 ? r4 : rows + r4;
-            hoff[q] = base_ + (size_t)hx + (size_t)n * wr(j0 - 2 + yy);
-            hdst[q] = f * us + yy * n + hx;
+            hoff[q] = base_ + (size_t)(i0 + hx) + (size_t)n * wr(j0 - 2 + yy);
+            hdst[q] = f * us + yy * pw + ox0 + hx;
         } else if (FACES && h == 4 * NY) {          // face y at y = j0 - 1
             hsrc[q] = (gptr)(k.face + N);
-            hoff[q] = base_ + (size_t)hx + (size_t)n * wr(j0 - 1);
-            hdst[q] = NS * us + R * n + hx;
+            hoff[q] = base_ + (size_t)(i0 + hx) + (size_t)n * wr(j0 - 1);
+            hdst[q] = NS * us + R * pw + ox0 + hx;
+        } else if (SEG) {                           // x halo: 4 NX + F1 cells of each row
+            constexpr int NJ = 4 * NX + F1 > 0 ? 4 * NX + F1 : 1;
+            const int jx = jb - (4 * NY + F1) * wd, yr = jx / NJ, e = jx - yr * NJ;
+            if (4 * NX + F1 > 0 && yr < rows) {
+                const int e4 = e & 3, xx = e4 < 2 ? e4 - 2 : wd + e4 - 2;   // -2, -1, wd, wd + 1
+                int fx = -1, ax = 0;
+#pragma unroll
+                for (int g = 0; g < NS; ++g)
+                    if ((XS >> g) & 1u) {
+                        if (e >= 4 * ax && e < 4 * ax + 4) {
+                            fx = g;
+                            hsrc[q] = (gptr)k.sf[g];
+                        }
+                        ++ax;
+                    }
+                if (fx >= 0) {
+                    hoff[q] = base_ + (size_t)wr(i0 + xx) + (size_t)n * (j0 + yr);
+                    hdst[q] = fx * us + (yr + 2) * pw + ox0 + xx;
+                } else {                            // face x at x = i0 - 1
+                    hsrc[q] = (gptr)k.face;
+                    hoff[q] = base_ + (size_t)wr(i0 - 1) + (size_t)n * (j0 + yr);
+                    hdst[q] = NS * us + yr * pw + ox0 - 1;
+                }
+            }
         }
     }
     // the z queues (fields read along z: planes kk - 2 .. kk + 2; others: slot 2 only)
@@ -3346,7 +3385,7 @@ __global__ void __launch_bounds__(kFlatFieldThreads) k_flat(Phys ph, DevState* s
     }
     typename K::Pts cur = k.load(col + nn * k0), nxt;
 #pragma unroll
-    for (int q = 0; q < kPer; ++q) nh[q] = hsrc[q][nn * (size_t)k0 + hoff[q]];
+    for (int q = 0; q < kHalo; ++q) nh[q] = hsrc[q][nn * (size_t)k0 + hoff[q]];
     T nq[NS], nfz = T(0), nfx = T(0), nfy = T(0);
     // queue heads at plane kq, own values at kv
     auto prefetch = [&](int kq, int kv) {
@@ -3369,16 +3408,16 @@ __global__ void __launch_bounds__(kFlatFieldThreads) k_flat(Phys ph, DevState* s
             for (int f = 0; f < NS; ++f)
                 if (((XS | YS) >> f) & 1u) U[f * us + ow + xi] = q5[f][2];
             if (FACES) {
-                FX[y * n + xi] = cfx;
-                FY[(y + 1) * n + xi] = cfy;
+                FX[y * pw + xi] = cfx;
+                FY[(y + 1) * pw + xi] = cfy;
             }
         }
 #pragma unroll
-        for (int q = 0; q < kPer; ++q)
+        for (int q = 0; q < kHalo; ++q)
             if (hdst[q] >= 0) U[hdst[q]] = nh[q];
         const size_t hp = nn * (size_t)clampk(kk + 1, k1 - 1);
 #pragma unroll
-        for (int q = 0; q < kPer; ++q) nh[q] = hsrc[q][hp + hoff[q]];
+        for (int q = 0; q < kHalo; ++q) nh[q] = hsrc[q][hp + hoff[q]];
         lds_barrier();
         T v[NS][13], fp[3], fm[3];
 #pragma unroll
@@ -3392,10 +3431,10 @@ __global__ void __launch_bounds__(kFlatFieldThreads) k_flat(Phys ph, DevState* s
                 v[f][4] = u[xp2];
             }
             if ((YS >> f) & 1u) {
-                v[f][5] = u[xi - 2 * n];
-                v[f][6] = u[xi - n];
-                v[f][7] = u[xi + n];
-                v[f][8] = u[xi + 2 * n];
+                v[f][5] = u[xi - 2 * pw];
+                v[f][6] = u[xi - pw];
+                v[f][7] = u[xi + pw];
+                v[f][8] = u[xi + 2 * pw];
             }
             if ((ZS >> f) & 1u) {
                 v[f][9] = q5[f][0];
@@ -3406,9 +3445,9 @@ __global__ void __launch_bounds__(kFlatFieldThreads) k_flat(Phys ph, DevState* s
         }
         if (FACES) {
             fp[0] = cfx;
-            fm[0] = FX[y * n + xm1];
+            fm[0] = FX[y * pw + xm1];
             fp[1] = cfy;
-            fm[1] = FY[y * n + xi];
+            fm[1] = FY[y * pw + xi];
             fp[2] = fzq[1];
             fm[2] = fzq[0];
         }
@@ -4290,8 +4329,14 @@ static unsigned flat_launch(const Launch& TL, hipStream_t s, const Phys& ph, con
     pt.cz = TL.cz;
     pt.nz = TL.nz;
     const size_t rows = (size_t)K::NS * (TL.rows + 4) + (K::FACES ? 2 * TL.rows + 1 : 0);
-    hipLaunchKernelGGL((k_flat<T, K>), TL.grid, TL.block, rows * ph.n * sizeof(T), s, pt,
-                       const_cast<DevState*>(st), k);
+    if (ph.n > kFlatFieldMaxN) {
+        const size_t lds = rows * (seg_width(ph.n, (int)TL.grid.x) + 4) * sizeof(T);
+        hipLaunchKernelGGL((k_flat<T, K, true>), TL.grid, TL.block, lds, s, pt,
+                           const_cast<DevState*>(st), k);
+    } else {
+        hipLaunchKernelGGL((k_flat<T, K, false>), TL.grid, TL.block, rows * ph.n * sizeof(T), s, pt,
+                           const_cast<DevState*>(st), k);
+    }
     return TL.nblocks;
 }
 template <typename T, class K>
@@ -4324,6 +4369,14 @@ Launch make_tiled_launch(int n, int batch, int cz_tile) {
         want = kTiledBlocks;
         least = 8;
         L.block = dim3(kTX, kTY, 1);
+    } else if (n > kFlatFieldMaxN) {
+        gx = (n + kSegMost - 1) / kSegMost;
+        const int w = seg_width(n, gx), rows = kFlatFieldThreads / w;
+        gy = (n + rows - 1) / rows;
+        L.rows = (n + gy - 1) / gy;
+        want = kSegBlocks;
+        least = 8;
+        L.block = dim3((L.rows * w + 63) / 64 * 64, 1, 1);
     } else {
         const int rows = flat_field_rows(n);
         if (!rows) return L;   // nblocks = 0: not available

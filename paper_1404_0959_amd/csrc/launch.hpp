@@ -37,8 +37,9 @@ Launch make_launch(int n, int batch = 1);
 Launch make_launch_shaped(int n, int batch, int bx, int cz);
 
 // Launch of the z-marching field kernels: on 64 x 8 tiles for n a multiple of 64
-// from 128 on, marching over at least 8 planes; else on flattened rows (rows
-// x-rows per block) where flat_field_rows allows; else nblocks is 0.  Blocks march
+// from 128 on, marching over at least 8 planes; else from 40 on on flattened rows
+// (rows x-rows per block), whole ones up to 128 (flat_field_rows) and segments of
+// them (seg_width) beyond; below 40 nblocks is 0.  Blocks march
 // over exactly min(cz_tile, n) planes when cz_tile > 0 (a tuned choice).
 // Flattened rows: as many as fit 512 threads (256 registers a thread in FP64), at
 // least 4, so that the y halo is no larger than the block's own rows: n <= 128.
@@ -53,6 +54,15 @@ constexpr int kFlatFieldMinN = 40, kFlatFieldMaxN = kFlatFieldThreads / kFlatFie
 constexpr int flat_field_rows(int n) {
     return n >= kFlatFieldMinN && n <= kFlatFieldMaxN ? kFlatFieldThreads / n : 0;
 }
+// Segments: the fewest per row of at most kSegMost columns, in whole 64-byte lines
+// of doubles, so 64 to 96 columns and 5 to 7 rows per 512 threads (whole rows of
+// 160 would leave 3 rows a y halo larger than themselves).  z is cut for
+// kSegBlocks blocks and marches of at least 8 planes, whatever the batch: half as
+// many blocks took 9 % longer for an FP64 step of 200^3 (6 % less at 136^3), twice
+// as many 1-2 % longer from 136^3 to 200^3, four times 3-7 %.
+constexpr int kSegBlocks = 512;
+constexpr int kSegMost = 96, kSegWidth = 64, kSegRows = 5;
+__host__ __device__ constexpr int seg_width(int n, int gx) { return ((n + gx - 1) / gx + 7) / 8 * 8; }
 Launch make_tiled_launch(int n, int batch = 1, int cz_tile = 0);
 
 // Launch of the CG kernel for fields of elem_bytes per value.

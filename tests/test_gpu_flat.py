@@ -138,3 +138,21 @@ def test_batched_cg_sums_as_a_single_run(P, precision, n, members):
             assert np.array_equal(a[k], b[k]), (m, k)
         s.close()
     ens.close()
+
+
+@pytest.mark.parametrize("precision,n,variant", [
+    ("fp64", 129, {}), ("fp64", 193, {}), ("fp64", 200, {}), ("fp32", 130, {}), ("fp32", 193, {}),
+    ("fp64", 136, dict(two_way=True, gravity=(0.1, 0.0, -1.0))), ("fp64", 131, dict(bdf2=True)),
+    ("fp64", 130, dict(mom_tol=1e-8)), ("fp64", 150, dict(fourier=True)),
+])
+def test_segmented_step_matches_gathered(P, monkeypatch, precision, n, variant):
+    """The same comparison beyond 128, where a block owns segments of its rows: a
+    last segment narrower than the others (57 of 72 columns at 129, 49 at 193, 56
+    at 200), a last block with fewer rows, and the x halo across the period."""
+    test_step_matches_gathered(P, monkeypatch, precision, n, variant)
+
+
+@pytest.mark.parametrize("n", [130, 161])
+def test_segmented_chebyshev_matches_oracle(P, ora, n):
+    """As above, with the polynomial's two launches on segments."""
+    test_chebyshev_matches_oracle(P, ora, n)
