@@ -196,13 +196,18 @@ constexpr int kPadW = 9;   // dy, dz in [-4, 4]
 // the product, weights as the A operand) are the kRY rows of the three output
 // planes an input plane reaches, held in a ring: column 4 s + oy is row oy of
 // the output plane in slot s (s = plane mod 3; columns 12-15 idle).  Input
-// plane by input plane, each of its (kRY + 2) rows and 3 x shifts is one
+// plane by input plane, each two of its (kRY + 2) rows times 3 x shifts are one
 // product whose weight operand the lane takes from the padded (dz, dy) grid at
 // the offsets of its column; a column whose plane lies outside the chunk reads
 // the grid's zeros.  After an input plane the output plane of its dz = +1 taps
 // is complete: the lanes of its slot store it and clear their accumulators.
 // Each input row is loaded once per plane, into its register right after its
 // product (a plane of products covers the load).  y = yscale * output, FP32.
+// The row items go into K = 32 products two by two, as in the 16 -> 16 layer: one
+// accumulator tuple holds all three planes, so a plane's products form one chain,
+// which the pairs halve with the loads and the weights' reads from LDS (33.4 us a
+// launch at 128^3 with single items, 25.1 so, the values the same bit for bit; the
+// layer's traffic at a large copy's rate takes 16).
 template <int ZC>
 __global__ void __launch_bounds__(256) k_conv16_final_zm(int n, int batch,
                                                          const uint16_t* __restrict__ in,
@@ -210,7 +215,7 @@ __global__ void __launch_bounds__(256) k_conv16_final_zm(int n, int batch,
                                                          float* __restrict__ yout, float yscale) {
     static_assert(kRY == 4, "three planes of kRY rows fit the 16 matrix columns");
     // wl[((dz + 4) kPadW + dy + 4) 3 + q][g]: channels 4g..4g+3 of tap (q - 1, dy, dz)
-    __shared__ v4s wl[kPadW * kPadW * 3 * 4];
+    __shared__ __align__(16) v4s wl[kPadW * kPadW * 3 * 4];
     for (int i = threadIdx.x; i < kPadW * kPadW * 3 * 4; i += blockDim.x) {
         const int g = i % 4, e = i / 4, q = e % 3, dy = (e / 3) % kPadW - 4, dz = e / (3 * kPadW) - 4;
         const bool reach = dy >= -1 && dy <= 1 && dz >= -1 && dz <= 1;
@@ -231,21 +236,21 @@ __global__ void __launch_bounds__(256) k_conv16_final_zm(int n, int batch,
     const size_t N = (size_t)n * n * n, nn = (size_t)n * n;
     const int m = lane & 15, g = lane >> 4;
     const int col = lane & 15, oy = col % kRY, slot = col / kRY;   // this lane's A row (output column)
-    const uint16_t* inb = in + (size_t)b * N * 16 + 4 * g;
-    // this lane's element offset of input row iy, shift q within a plane
-    constexpr int kItemsF = (kRY + 2) * 3;
-    int off[kItemsF];
+    // pair it: the items (input row iy, shift q) 2 it in the lanes' groups 0-1 and
+    // 2 it + 1 in groups 2-3, 8 channels of a cell per lane
+    const uint16_t* inb = in + (size_t)b * N * 16 + 8 * (g & 1);
+    int off[kPairs];
 #pragma unroll
-    for (int it = 0; it < kItemsF; ++it) {
-        const int iy = it / 3, q = it % 3;
+    for (int it = 0; it < kPairs; ++it) {
+        const int r = 2 * it + (g >> 1), iy = r / 3, q = r % 3;
         off[it] = (n * wrapn(j0 - 1 + iy, n) + wrapn(iseg * 16 + m + q - 1, n)) * 16;
     }
     auto plane_ptr = [&](int t) { return inb + nn * 16 * (size_t)wrapn(k0 - 1 + t, n); };
-    v4s a[kItemsF];
+    v8s a[kPairs];
     {
         const uint16_t* pb = plane_ptr(0);
 #pragma unroll
-        for (int it = 0; it < kItemsF; ++it) a[it] = *reinterpret_cast<const v4s*>(pb + off[it]);
+        for (int it = 0; it < kPairs; ++it) a[it] = *reinterpret_cast<const v8s*>(pb + off[it]);
     }
     v4f acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
@@ -257,12 +262,11 @@ __global__ void __launch_bounds__(256) k_conv16_final_zm(int n, int batch,
         // the grid's zeros (dz = 4) when it is outside the chunk or the slot idle
         const int oz = t - 2 + ((slot - (t - 2) % 3 + 3) % 3);
         const int dz = slot < 3 && oz >= 0 && oz < ZC ? t - 1 - oz : 4;
-        const v4s* wb = wl + (((dz + 4) * kPadW + (3 - oy)) * 3) * 4 + g;
+        const v8s* wb = reinterpret_cast<const v8s*>(wl + (((dz + 4) * kPadW + (3 - oy)) * 3) * 4) + g;
 #pragma unroll
-        for (int it = 0; it < kItemsF; ++it) {
-            const int iy = it / 3, q = it % 3;
-            acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(wb[(iy * 3 + q) * 4], a[it], acc, 0, 0, 0);
-            if (more) a[it] = *reinterpret_cast<const v4s*>(pn + off[it]);
+        for (int it = 0; it < kPairs; ++it) {
+            acc = mfma_k32(wb[4 * it], a[it], acc);
+            if (more) a[it] = *reinterpret_cast<const v8s*>(pn + off[it]);
         }
         // output plane t - 2 is complete: lane (g, m) holds rows 4 g + e of
         // cell m, so the lanes of its slot store rows 0..3 and clear them
@@ -794,10 +798,7 @@ constexpr int kPackAll = kPackForward + 2 * kTapOps + 2 * kPairOps;
 
 // Every operand in one launch (one kernel per operand took 11 launches, a
 // fifth of the network's time on a 32^3 grid).
-__global__ void __launch_bounds__(256) k_pack(const float* __restrict__ w, Packed* __restrict__ p,
-                                              int count) {
-    int t = blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= count) return;
+__device__ inline void pack_operand(const float* __restrict__ w, Packed* __restrict__ p, int t) {
     const float* w1 = w + 2 * 16 * 27;
     const float* w2 = w1 + 16 * 16 * 27;
     const float* w3 = w2 + 16 * 16 * 27;
@@ -827,16 +828,39 @@ __global__ void __launch_bounds__(256) k_pack(const float* __restrict__ w, Packe
     p->bpair[l][t - l * kPairOps] = pack_pairs(l ? w2 : w1, true, t - l * kPairOps);
 }
 
-// Network input: channel-last BF16 [cell][4] = (x0, x1, 0, 0) from FP32 [cell][2].
-__global__ void k_input_bf16(const float* __restrict__ x, uint16_t* __restrict__ xb, size_t cells) {
-    size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    size_t stride = (size_t)gridDim.x * blockDim.x;
+__global__ void __launch_bounds__(256) k_pack(const float* __restrict__ w, Packed* __restrict__ p,
+                                              int count) {
+    const int t = blockIdx.x * blockDim.x + threadIdx.x;
+    if (t < count) pack_operand(w, p, t);
+}
+
+// The start of a pass in one launch: the first blocks pack the weights (count of
+// Packed's operands), the others convert the network's input to channel-last
+// BF16 [cell][4] = (x0, x1, 0, 0) from FP32 [cell][2].  Each was a launch of its
+// own, 5 us for the pack.
+__global__ void __launch_bounds__(256) k_begin(const float* __restrict__ w, Packed* __restrict__ p,
+                                               int count, const float* __restrict__ x,
+                                               uint16_t* __restrict__ xb, size_t cells) {
+    const unsigned nb = (unsigned)(count + 255) / 256;
+    if (blockIdx.x < nb) {
+        const int t = blockIdx.x * 256 + threadIdx.x;
+        if (t < count) pack_operand(w, p, t);
+        return;
+    }
+    size_t i = (size_t)(blockIdx.x - nb) * 256 + threadIdx.x;
+    const size_t stride = (size_t)(gridDim.x - nb) * 256;
     for (; i < cells; i += stride) {
         xb[4 * i + 0] = f2bf(x[2 * i + 0]);
         xb[4 * i + 1] = f2bf(x[2 * i + 1]);
         xb[4 * i + 2] = 0;
         xb[4 * i + 3] = 0;
     }
+}
+static void begin(hipStream_t s, const float* w, Packed* p, int count, const float* x, uint16_t* xb,
+                  size_t cells) {
+    const unsigned nb = (unsigned)(count + 255) / 256;
+    const unsigned lin = (unsigned)std::min<size_t>((cells + 255) / 256, 65536);
+    hipLaunchKernelGGL(k_begin, dim3(nb + lin), dim3(256), 0, s, w, p, count, x, xb, cells);
 }
 
 // MSE loss partials and the output gradient dy = 2 (y - t) / count as BF16 [cell][4].
@@ -1102,9 +1126,7 @@ pisoc_status pisoc_net_forward(int32_t n, int32_t batch, const float* d_w, const
     char* ws = reinterpret_cast<char*>(d_ws);
     const size_t cells = (size_t)batch * n * n * n;
     uint16_t* x4 = reinterpret_cast<uint16_t*>(ws + L.x4);
-    hipLaunchKernelGGL(k_input_bf16, dim3((unsigned)std::min<size_t>((cells + 255) / 256, 65536)),
-                       dim3(256), 0, s, d_x, x4, cells);
-    net_pack_forward(s, d_w, ws + L.wf);
+    begin(s, d_w, reinterpret_cast<Packed*>(ws + L.wf), kPackForward, d_x, x4, cells);
     net_forward(s, n, batch, ws + L.wf, x4, reinterpret_cast<uint16_t*>(ws + L.a1),
                 reinterpret_cast<uint16_t*>(ws + L.a2), d_y, 1.f);
     return hipGetLastError() == hipSuccess ? PISOC_OK : PISOC_ERR_HIP;
@@ -1116,10 +1138,8 @@ static void grad_forward(hipStream_t s, const NetWs& L, char* ws, int n, int bat
                          const float* d_x) {
     auto U = [&](size_t off) { return reinterpret_cast<uint16_t*>(ws + off); };
     const size_t cells = (size_t)batch * n * n * n;
-    const unsigned lin = (unsigned)std::min<size_t>((cells + 255) / 256, 65536);
-    hipLaunchKernelGGL(k_input_bf16, dim3(lin), dim3(256), 0, s, d_x, U(L.x4), cells);
     Packed* p = reinterpret_cast<Packed*>(ws + L.wf);
-    hipLaunchKernelGGL(k_pack, dim3((kPackAll + 255) / 256), dim3(256), 0, s, d_w, p, kPackAll);
+    begin(s, d_w, p, kPackAll, d_x, U(L.x4), cells);
     conv4_taps<false>(s, n, batch, U(L.x4), p->taps[0], nullptr, U(L.a1));
     forward_from(s, n, batch, p, U(L.a1), U(L.a2), U(L.a3), reinterpret_cast<float*>(ws + L.y), 1.f);
 }
