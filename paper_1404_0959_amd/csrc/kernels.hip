@@ -945,7 +945,6 @@ __global__ void __launch_bounds__(kBlock) k_refine(Phys ph, DevState* st,
     if (MEMBER_FIRST()) {
         (st + mem_)->pcg.it_stop = kIterInf;
         (st + mem_)->pcg.converged = 0;
-        (st + mem_)->pcg.iters = 0;
     }
 }
 
@@ -2855,10 +2854,8 @@ __global__ void __launch_bounds__(kBlock) k_sum_affine_sq(Phys ph, const DevStat
 // One block per member: totals of nv partial columns (sums) of member
 // blockIdx.x into st[member].red[off .. off + nv).
 __global__ void __launch_bounds__(kBlock) k_finalize_sums(const double* part, unsigned nbt,
-                                                          int batch, int nv, DevState* st, int off,
-                                                          int honor_skip) {
+                                                          int batch, int nv, DevState* st, int off) {
     const int m = blockIdx.x;
-    if (honor_skip && st[m].pcg.skip) return;   // a skipped refinement round wrote no partials
     for (int c = 0; c < nv; ++c) {
         double t[1];
         reduce_member<1, 0u>(part + (size_t)c * nbt, nbt, batch, m, t);
@@ -2965,47 +2962,60 @@ __global__ void k_set_affine(DevState* st, int batch, int mode, double N) {
     st[m].aff[1] = b;
 }
 
-// Record a solve of corrector `corr` in every member's step record.
-// add: the solve just finished counts -- its iterations are added to the
-// step's total and kept as the first solve's (round <= 1: the FP64 solve or
-// the first FP32 round) or as the largest later round's.  fin (1: residual
-// from the last CG check, 2: from red[0] = ||r64||^2 after refinement):
-// the final relative residual against the original ||b|| and the refinement
-// rounds (round) are stored, and flag 1 is raised unless the residual meets
-// the requested tolerance.
-__global__ void k_record_solve(DevState* st, int batch, int corr, int round, int add, int fin) {
+// The iterations of the solve of corrector corr just finished: added to the
+// step's total and kept as the first solve's (round <= 1: the FP64 solve or the
+// first FP32 round) or as the largest later round's.
+__device__ inline void record_iters(DevState& d, int corr, int round) {
+    const int it = d.pcg.iters;
+    d.it_corr[corr] += it;
+    if (round <= 1) d.it_first[corr] = it;
+    else if (it > d.it_later[corr]) d.it_later[corr] = it;
+}
+
+// The end of corrector corr's solves in every member's step record: the final
+// relative residual against the original ||b|| (refined: ||r64||^2 in red[0],
+// else the last CG check's) and the refinement rounds; flag 1 is raised unless
+// it meets the requested tolerance.  Without refinement the solve's iterations
+// are recorded too.  The next fresh solve's tolerance is tol2 (with it and with
+// k_refine_end an FP32 step makes four launches fewer than with a launch for
+// each tolerance and record: 377 against 365 us at 32^3, 462 and 459 in FP64,
+// which makes two fewer, at 48^3).
+__global__ void k_record_solve(DevState* st, int batch, int corr, int round, int refined,
+                               double tol2) {
     const int m = blockIdx.x * blockDim.x + threadIdx.x;
     if (m >= batch) return;
     DevState& d = st[m];
-    if (add) {
-        const int it = d.pcg.iters;
-        d.it_corr[corr] += it;
-        if (round <= 1) d.it_first[corr] = it;
-        else if (it > d.it_later[corr]) d.it_later[corr] = it;
-    }
-    if (!fin) return;
-    const double rr = fin == 2 ? d.red[0] : d.pcg.rr;
+    if (!refined) record_iters(d, corr, round);
+    const double rr = refined ? d.red[0] : d.pcg.rr;
     d.rel_corr[corr] = d.pcg.bb > 0.0 ? sqrt(rr / d.pcg.bb) : 0.0;
     d.rounds_corr[corr] = round;
     if (!(rr <= d.pcg.tol_final * d.pcg.bb)) d.flags |= 1;
+    d.pcg.tol2 = tol2;
+    d.pcg.skip = 0;
 }
 
-// Tolerance of the next FP32 refinement round of every member from red[0] =
-// ||r64||^2 and the original ||b||^2 (pcg.bb): reduce the current residual
-// to half the requested one, but by no less than the factor tau_min (and at
-// least by 1/2).  A member already within p_tol gets skip = 1: the round's
-// solve stops at k = 0 without touching x, and its refinement and the totals
-// of its partials return at once (x64, xf and red[0] keep the values of the
-// last round that ran).  Rounds beyond convergence occur in captured steps,
-// whose round count is fixed.
-__global__ void k_set_tol_refine(DevState* st, int batch, double tau_min) {
-    const int m = blockIdx.x * blockDim.x + threadIdx.x;
-    if (m >= batch) return;
+// The end of refinement round `round` (>= 1), one block per member: the round's
+// CG iterations into the step record, the total of the refinement's column
+// ||r64||^2 into red[0], and the tolerance of the next round from it and the
+// original ||b||^2 (pcg.bb): reduce the current residual to half the requested
+// one, but by no less than the factor tau_min (and at least by 1/2).  A member
+// already within p_tol gets skip = 1: the next round's solve stops at k = 0
+// without touching x, and its refinement and this kernel return at once (x64, xf
+// and red[0] keep the values of the last round that ran).  Rounds beyond
+// convergence occur in captured steps, whose round count is fixed.
+__global__ void __launch_bounds__(kBlock) k_refine_end(const double* part, unsigned nbt, int batch,
+                                                       DevState* st, int corr, int round,
+                                                       double tau_min) {
+    const int m = blockIdx.x;
     DevState& d = st[m];
-    const double rr = d.red[0], bb = d.pcg.bb;
-    d.pcg.skip = 0;
+    if (d.pcg.skip) return;   // the whole block: a skipped round wrote no partials
+    double t[1];
+    reduce_member<1, 0u>(part, nbt, batch, m, t);
+    if (flat_tid() != 0) return;
+    record_iters(d, corr, round);
+    const double rr = t[0], bb = d.pcg.bb;
+    d.red[0] = rr;
     if (rr <= d.pcg.tol_final * bb || !(bb > 0.0)) {
-        // done: the round's solve and refinement return at once
         d.pcg.tol2 = 1.0;
         d.pcg.skip = 1;
         return;
@@ -3023,11 +3033,14 @@ __global__ void k_set_tol(DevState* st, int batch, double tol2) {
     st[m].pcg.skip = 0;
 }
 
-// Clear the step flags and the step record of every member (start of a step).
-__global__ void k_clear_flags(DevState* st, int batch) {
+// Clear the step flags and the step record of every member (start of a step)
+// and set the first solve's tolerance.
+__global__ void k_clear_flags(DevState* st, int batch, double tol2) {
     const int m = blockIdx.x * blockDim.x + threadIdx.x;
     if (m >= batch) return;
     st[m].flags = 0;
+    st[m].pcg.tol2 = tol2;
+    st[m].pcg.skip = 0;
     for (int c = 0; c < kMaxCorr; ++c) {
         st[m].it_corr[c] = 0;
         st[m].rel_corr[c] = 0.0;
@@ -3689,7 +3702,6 @@ struct TiledRefineFromZero : TiledBase<T> {
     __device__ void first(DevState* d) const {
         d->pcg.it_stop = kIterInf;
         d->pcg.converged = 0;
-        d->pcg.iters = 0;
     }
 };
 
@@ -5032,9 +5044,9 @@ void Ops<T>::sum_affine_sq(const Launch& L, hipStream_t s, const Phys& ph, const
 }
 
 void finalize_sums(hipStream_t s, const double* part, unsigned nbt, int batch, int nv,
-                   DevState* st, int off, bool honor_skip) {
+                   DevState* st, int off) {
     hipLaunchKernelGGL(k_finalize_sums, dim3(batch), dim3(64, 4), 0, s, part, nbt, batch, nv, st,
-                       off, honor_skip ? 1 : 0);
+                       off);
 }
 void sum_partials(hipStream_t s, const double* part, unsigned nb, double* dst) {
     hipLaunchKernelGGL(k_sum_partials, dim3(1), dim3(64, 4), 0, s, part, nb, dst);
@@ -5051,9 +5063,10 @@ void commit(hipStream_t s, DevState* st, int batch) {
 void clear_acc(hipStream_t s, DevState* st, int batch) {
     hipLaunchKernelGGL(k_clear_acc, dim3((batch + 63) / 64), dim3(64), 0, s, st, batch);
 }
-void set_tol_refine(hipStream_t s, DevState* st, int batch, double tau_min) {
-    hipLaunchKernelGGL(k_set_tol_refine, dim3((batch + 63) / 64), dim3(64), 0, s, st, batch,
-                       tau_min);
+void refine_end(hipStream_t s, const double* part, unsigned nbt, int batch, DevState* st, int corr,
+                int round, double tau_min) {
+    hipLaunchKernelGGL(k_refine_end, dim3(batch), dim3(64, 4), 0, s, part, nbt, batch, st, corr,
+                       round, tau_min);
 }
 void set_tol(hipStream_t s, DevState* st, int batch, double tol2) {
     hipLaunchKernelGGL(k_set_tol, dim3((batch + 63) / 64), dim3(64), 0, s, st, batch, tol2);
@@ -5061,12 +5074,13 @@ void set_tol(hipStream_t s, DevState* st, int batch, double tol2) {
 void set_affine(hipStream_t s, DevState* st, int batch, int mode, double N) {
     hipLaunchKernelGGL(k_set_affine, dim3((batch + 63) / 64), dim3(64), 0, s, st, batch, mode, N);
 }
-void record_solve(hipStream_t s, DevState* st, int batch, int corr, int round, int add, int fin) {
+void record_solve(hipStream_t s, DevState* st, int batch, int corr, int round, bool refined,
+                  double tol2) {
     hipLaunchKernelGGL(k_record_solve, dim3((batch + 63) / 64), dim3(64), 0, s, st, batch, corr,
-                       round, add, fin);
+                       round, refined ? 1 : 0, tol2);
 }
-void clear_flags(hipStream_t s, DevState* st, int batch) {
-    hipLaunchKernelGGL(k_clear_flags, dim3((batch + 63) / 64), dim3(64), 0, s, st, batch);
+void clear_flags(hipStream_t s, DevState* st, int batch, double tol2) {
+    hipLaunchKernelGGL(k_clear_flags, dim3((batch + 63) / 64), dim3(64), 0, s, st, batch, tol2);
 }
 
 template <typename T>

@@ -334,10 +334,9 @@ struct Ops {
 };
 
 // Per member: totals of nv partial columns (written by a launch of nbt blocks
-// over `batch` members) into st[m].red[off ..]; honor_skip: not for a member
-// whose refinement round was skipped (pcg.skip).
+// over `batch` members) into st[m].red[off ..].
 void finalize_sums(hipStream_t s, const double* part, unsigned nbt, int batch, int nv,
-                   DevState* st, int off, bool honor_skip = false);
+                   DevState* st, int off);
 // Total of nb partials (one column) into dst[0].
 void sum_partials(hipStream_t s, const double* part, unsigned nb, double* dst);
 // Per member: end-of-step mass budget and flags.
@@ -352,15 +351,19 @@ void step_finish(hipStream_t s, const Phys& ph, DevState* st, const double* part
 void commit(hipStream_t s, DevState* st, int batch);
 // Per member: clear the accumulators.
 void clear_acc(hipStream_t s, DevState* st, int batch);
-// Per member: tolerance of the next FP32 refinement round (see k_set_tol_refine).
-void set_tol_refine(hipStream_t s, DevState* st, int batch, double tau_min);
+// Per member: the end of a refinement round, from its column ||r64||^2 of nbt
+// partials (see k_refine_end).
+void refine_end(hipStream_t s, const double* part, unsigned nbt, int batch, DevState* st, int corr,
+                int round, double tau_min);
 // Per member: CG tolerance (squared) for the next solve.
 void set_tol(hipStream_t s, DevState* st, int batch, double tol2);
 // Per member: affine coefficients for sum_affine_sq (see k_set_affine).
 void set_affine(hipStream_t s, DevState* st, int batch, int mode, double N);
-// Per member: record a solve of corrector corr in the step record (see k_record_solve).
-void record_solve(hipStream_t s, DevState* st, int batch, int corr, int round, int add, int fin);
-// Per member: clear the step flags.
-void clear_flags(hipStream_t s, DevState* st, int batch);
+// Per member: corrector corr's solves in the step record, and the next fresh
+// solve's tolerance (see k_record_solve).
+void record_solve(hipStream_t s, DevState* st, int batch, int corr, int round, bool refined,
+                  double tol2);
+// Per member: clear the step flags; the first solve's tolerance.
+void clear_flags(hipStream_t s, DevState* st, int batch, double tol2);
 
 }  // namespace pisoc

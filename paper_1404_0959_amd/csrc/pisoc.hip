@@ -565,6 +565,14 @@ pisoc_status run_pcg(pisoc_ctx* ctx, const CgVecs<T>& v, bool fresh, int iters, 
     return PISOC_OK;
 }
 
+// The squared tolerance, relative to ||b||, of a corrector's first solve: the
+// requested one, or the first inner FP32 solve's tau0 (solve_fp32).
+double fresh_tol2(const pisoc_params& p) {
+    const double t = p.precision == PISOC_FP64 ? p.p_tol
+                                               : std::min(0.5, std::max(0.5 * p.p_tol, p.inner_tol));
+    return t * t;
+}
+
 // The initial guess of one pressure solve, every member: the learned one
 // (scaled inputs from the system just set up, the network on the matrix cores,
 // g = s1 y) or the previous step's solution of the same corrector (g = gprev);
@@ -689,7 +697,7 @@ pisoc_status enqueue_front(pisoc_ctx* ctx, StepPtrs<T>& S, bool cfl_ready) {
     const Launch& L = ctx->L;
     hipStream_t s = ctx->stream;
     DevState* st = ctx->st;
-    clear_flags(s, st, ctx->batch);
+    clear_flags(s, st, ctx->batch, fresh_tol2(p));
     if (!cfl_ready) {
         timed(ctx, KC_CFL, 4, -1, [&] { O::cfl(L, s, ph, st, S.rn, S.phin, ctx->part(PS_CFL)); });
         ctx->nb_cfl = L.nblocks;
@@ -923,9 +931,7 @@ void solve_fp32(pisoc_ctx* ctx, StepPtrs<float>& S, int corr, bool guess, bool e
     const int B = ctx->batch;
     double* xa = S.x64a;
     double* xb = S.x64b;
-    const double tau0 = std::min(0.5, std::max(0.5 * p.p_tol, p.inner_tol));
     *err = PISOC_OK;
-    set_tol(s, ctx->st, B, tau0 * tau0);
     int most = 0;
     // An eager first round does not wait for the host: it runs the
     // iterations of the last step's first round plus kSpecMargin, the last
@@ -937,7 +943,6 @@ void solve_fp32(pisoc_ctx* ctx, StepPtrs<float>& S, int corr, bool guess, bool e
     if ((*err = run_pcg<float>(ctx, cg_vecs(S), true, cap0, false, nullptr, !guess, ctx->nb_start,
                                cap0)) != PISOC_OK)
         return;
-    record_solve(s, ctx->st, B, corr, /*round=*/1, /*add=*/1, /*fin=*/0);
     bool waited = false;   // the host has seen the state since the first round
     const int max_rounds = eager ? p.max_refine : ctx->rounds;
     int round = 0;
@@ -958,7 +963,7 @@ void solve_fp32(pisoc_ctx* ctx, StepPtrs<float>& S, int corr, bool guess, bool e
         else sol_in_x = true;
         ++round;
         // column 1 (||r64||^2) of the 3 columns written with nb_ref blocks
-        finalize_sums(s, ctx->part(PS_U) + nb_ref, nb_ref, B, 1, ctx->st, 0, true);
+        refine_end(s, ctx->part(PS_U) + nb_ref, nb_ref, B, ctx->st, corr, round, p.inner_tol);
         if (round >= max_rounds) break;
         if (eager) {
             if ((*err = sync_state(ctx)) != PISOC_OK) return;
@@ -985,21 +990,19 @@ void solve_fp32(pisoc_ctx* ctx, StepPtrs<float>& S, int corr, bool guess, bool e
             }
             sol_in_x = false;
         }
-        set_tol_refine(s, ctx->st, B, p.inner_tol);
         // the inner correction of this round starts from zero (not written)
         const int pairs = eager ? std::max(2, ctx->pred_later) : ctx->cap_later;
         if ((*err = run_pcg<float>(ctx, cg_vecs(S), false, pairs, eager,
                                    &most, true, nb_ref, eager ? 0 : pairs)) != PISOC_OK)
             return;
         if (eager) ctx->pred_later = most;
-        record_solve(s, ctx->st, B, corr, round + 1, /*add=*/1, /*fin=*/0);
     }
     if (eager && ctx->prof.on && !waited) {
         // attribute the first round's launches before later solves add more
         if ((*err = sync_state(ctx)) != PISOC_OK) return;
         ctx->prof.resolve(first_stop(ctx, corr));
     }
-    record_solve(s, ctx->st, B, corr, round, /*add=*/0, /*fin=*/2);
+    record_solve(s, ctx->st, B, corr, round, /*refined=*/true, fresh_tol2(p));
     // the corrector uses the FP32 copy of the FP64 solution, which the last
     // refinement wrote to xf: exchange the two buffers' roles for the rest of
     // the step (x is free again until the next solve writes it); after a
@@ -1133,7 +1136,6 @@ pisoc_status enqueue_step(pisoc_ctx* ctx, bool eager) {
         if constexpr (sizeof(T) == sizeof(float)) {
             solve_fp32(ctx, S, corr, guess, eager, &err);
         } else {
-            set_tol(s, ctx->st, ctx->batch, p.p_tol * p.p_tol);
             int most = 0;
             const int pairs =
                 eager ? (ctx->pred_first[corr] > 0 ? ctx->pred_first[corr] : 8) : ctx->caps[corr];
@@ -1142,7 +1144,7 @@ pisoc_status enqueue_step(pisoc_ctx* ctx, bool eager) {
             err = run_pcg<T>(ctx, cg_vecs(S), true, pairs, eager, &most,
                              !guess, ctx->nb_start, eager ? 0 : pairs);
             if (eager) ctx->pred_first[corr] = most;
-            record_solve(s, ctx->st, ctx->batch, corr, /*round=*/0, /*add=*/1, /*fin=*/1);
+            record_solve(s, ctx->st, ctx->batch, corr, /*round=*/0, /*refined=*/false, fresh_tol2(p));
         }
         if (err != PISOC_OK) return err;
         if (audit && guess) (void)hipEventRecord(ctx->audit.ev[corr][2], s);
