@@ -264,12 +264,12 @@ def extras_run(P, torch, case, args):
         torch.cuda.synchronize()
         return (time.perf_counter() - t) / reps
     diag = {}
-    # bytes per cell: spectrum, per component: the real field read (8), three
-    # FFT passes reading and writing the complex field (3 x 32), the shell
-    # binning reading it (16); Q: 3 velocity words read, Q written; filtered
+    # bytes per cell: spectrum, per component: the real field read and the
+    # half-complex one written along x (8 + 8), read and written along y (16),
+    # read along z and binned (8); Q: 3 velocity words read, Q written; filtered
     # statistics: u read (24) and nine filtered fields written (72), then read
     # back (72)
-    for name, fn, bpc in (("spectrum", lambda: P.spectrum(u), 3 * (8 + 96 + 16)),
+    for name, fn, bpc in (("spectrum", lambda: P.spectrum(u), 3 * (8 + 8 + 16 + 8)),
                           ("qcriterion", lambda: P.qcriterion(u), 32),
                           ("filtered_stats", lambda: P.sgs_stats(u), 168)):
         t = time_it(fn)
