@@ -21,6 +21,7 @@ struct Launch {
     int rows = 0;       // and x-rows per block of its flat form (0: another form)
     int sub = 0;        // and planes per partial sum of a block (cz, or a divisor of it)
     unsigned nparts = 0;   // and partial sums per column, all members
+    bool gathered = false;   // a fused pass on the gathered launch (k_gather)
     bool nt = false;    // and its once-read fields streamed past the caches (make_spmv_launch)
 };
 

@@ -287,6 +287,7 @@ struct pisoc_ctx {
     Phys ph;
     Launch L;
     Launch TL;      // tiled z-marching launch of the field kernels (nblocks = 0: none)
+    bool fuse = true;   // the fused passes on the gathered launch where TL has none
     unsigned nb_start = 0;   // partials in PS_U of the current solve's start (its set-up kernel)
     unsigned nb_mass = 0;    // partials in PS_MASS (the last corrector update)
     // Courant partials of the current state: nb_cfl of them at cfl_part,
@@ -815,6 +816,13 @@ void enqueue_corr_setup(pisoc_ctx* ctx, StepPtrs<T>& S, int corr, bool guess) {
     }
 }
 
+// Launch of the fused passes: the staged one, else the gathered one.
+Launch fused_pass(const pisoc_ctx* ctx) {
+    Launch F = ctx->TL.nblocks || !ctx->fuse ? ctx->TL : ctx->L;
+    F.gathered = F.nblocks && !ctx->TL.nblocks;
+    return F;
+}
+
 template <typename T>
 void enqueue_corr_finish(pisoc_ctx* ctx, StepPtrs<T>& S, int corr) {
     using O = Ops<T>;
@@ -825,12 +833,12 @@ void enqueue_corr_finish(pisoc_ctx* ctx, StepPtrs<T>& S, int corr) {
     const bool cap = S.snap && corr == 0;
     T* ucur = ucur_of(ctx, S);
     const bool last = corr == ctx->prm.n_corr - 1;
-    if (ctx->TL.nblocks) {
-        // flux correction and update in one tiled pass (words: w, p0, p', phiH x3,
+    if (const Launch FL = fused_pass(ctx); FL.nblocks) {
+        // flux correction and update in one pass (words: w, p0, p', phiH x3,
         // HbyA x3, rho^n, a_P read; phi x3, rho_k, u x3 written)
         timed(ctx, KC_CORR_UPDATE, 18, -1, [&] {
             // the last pass also leaves the Courant partials of the new state
-            ctx->nb_mass = O::corr_finish_fused(ctx->TL, s, ph, ctx->st, last, S.p0, S.x, S.w,
+            ctx->nb_mass = O::corr_finish_fused(FL, s, ph, ctx->st, last, S.p0, S.x, S.w,
                                                 S.phiH, S.phik, cap ? S.snap + 3 * N : nullptr,
                                                 S.rn, S.hb, S.aP, S.rk, ucur, ctx->part(PS_MASS));
         });
@@ -882,10 +890,10 @@ void enqueue_dust(pisoc_ctx* ctx, StepPtrs<T>& S) {
             }
             // two-way coupling: the class's face fluxes add up to the next step's F_d
             const double fdw = S.fdk ? (c == 0 ? 3.0 : 6.0) : 0.0;
-            if (ctx->TL.nblocks) {
-                // face fluxes and finish in one tiled pass (words: Y, G, rho_j read, rho_j' written)
+            if (const Launch FL = fused_pass(ctx); FL.nblocks) {
+                // face fluxes and finish in one pass (words: Y, G, rho_j read, rho_j' written)
                 timed(ctx, KC_DUST_FINISH, 6 + fdw, -1, [&] {
-                    nb_dust = O::dust_finish_fused(ctx->TL, s, phc, st, yin, S.G, S.rj + c * N,
+                    nb_dust = O::dust_finish_fused(FL, s, phc, st, yin, S.G, S.rj + c * N,
                                                    S.rj1 + c * N, ctx->part(PS_DUST + 2 * c),
                                                    S.fdk, c == 0);
                 });
@@ -1331,7 +1339,10 @@ pisoc_status init_ctx(pisoc_ctx* ctx, const pisoc_params* mprm, int batch, char*
     ctx->TL = make_tiled_launch(prm->n, batch);
     ctx->TS = make_spmv_launch(prm->n, batch, prm->precision == PISOC_FP64 ? 8 : 4);
     // PISOC_UNTILED=1 selects the untiled kernels (kernel-comparison tests)
-    if (const char* e = std::getenv("PISOC_UNTILED"); e && e[0] == '1') ctx->TL = ctx->TS = Launch{};
+    if (const char* e = std::getenv("PISOC_UNTILED"); e && e[0] == '1') {
+        ctx->TL = ctx->TS = Launch{};
+        ctx->fuse = false;
+    }
     // (the tiled forms carry the Fourier closure and BDF2 as the gathered ones)
     ctx->L = make_launch(prm->n, batch);
     ctx->ph = make_phys(prm, ctx->L, batch);

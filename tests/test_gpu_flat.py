@@ -156,3 +156,14 @@ def test_segmented_step_matches_gathered(P, monkeypatch, precision, n, variant):
 def test_segmented_chebyshev_matches_oracle(P, ora, n):
     """As above, with the polynomial's two launches on segments."""
     test_chebyshev_matches_oracle(P, ora, n)
+
+
+@pytest.mark.parametrize("precision,n,variant", [
+    ("fp64", 9, {}), ("fp64", 17, {}), ("fp64", 39, {}), ("fp32", 16, {}), ("fp32", 33, {}),
+    ("fp64", 20, dict(two_way=True, gravity=(0.1, 0.0, -1.0))), ("fp64", 24, dict(bdf2=True)),
+    ("fp64", 32, dict(fourier=True)),
+])
+def test_small_fused_passes_match_separate(P, monkeypatch, precision, n, variant):
+    """The same comparison below 40: the corrector's and the dust's fused passes on
+    the gathered launch against the separate kernels."""
+    test_step_matches_gathered(P, monkeypatch, precision, n, variant)
