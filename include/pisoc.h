@@ -318,7 +318,11 @@ int32_t pisoc_profile_read(const pisoc_ctx* ctx, pisoc_kernel_stat* h_out, int32
  * parameter must be equal.  The ensemble creates and owns its HIP streams; the
  * calls that step or read it synchronise them.
  *
- * PISOC_ENS_EAGER steps like pisoc_step, per class.  PISOC_ENS_GRAPH replays
+ * PISOC_ENS_EAGER steps like pisoc_step, per class; the classes' steps may be
+ * enqueued at the same time, by up to four host threads that live for the step.
+ * If a class's step fails, the classes before it (in order of first appearance)
+ * have advanced and keep the step; it and those after it keep their state, as if
+ * the step had not been called.  PISOC_ENS_GRAPH replays
  * one captured HIP graph per step for each size class, on the class's stream
  * (the classes' replays overlap): each pressure solve
  * runs a fixed number of CG iterations (sized from the iterations the members

@@ -1961,10 +1961,15 @@ namespace {
 // next class as it ends one.  Five steps with the learned guess, FP32: 24 members
 // of 32, 32, 48 and 64 cells a side 16.0 ms one class after the other, 13.2 so;
 // 8 members 8.8 and 6.8.
-// The caller commits the classes in their order, up to the first that failed:
-// later ones have then not advanced.  One class after the other still, each
-// tried only after those before it were committed, where there is a single class
-// or the learned-guess audit is on (it compares timings of its own solves).
+// The caller commits the classes in their order, up to the first that failed: those
+// after it have then not advanced, and a try leaves nothing else of theirs behind --
+// it writes scratch, and the iteration counts that size the next step's launches,
+// which are put back (drop_from).  One class after the other still, each tried only
+// after those before it were committed, where a try writes what the next one or
+// the caller reads (the previous-step guess's solutions, the captured pressure
+// system), where the learned-guess audit is on (it compares timings of its own
+// solves), with a single class, or with a single host thread to run on (each spins
+// in its host waits).
 constexpr size_t kEnsThreads = 4;
 
 struct EagerRound {
@@ -1973,19 +1978,29 @@ struct EagerRound {
     int dev = 0;
     std::vector<std::vector<pisoc_step_info>> info;   // of each class's members
     std::vector<pisoc_status> status;
+    size_t threads = std::min<size_t>(kEnsThreads, std::thread::hardware_concurrency());
+    struct Pred {
+        int first[PISOC_MAX_CORR], later;
+    };
+    std::vector<Pred> pred;   // each class's predictions before its try
 
-    explicit EagerRound(pisoc_ens* ens) : e(ens), together(ens->cls.size() > 1) {
+    explicit EagerRound(pisoc_ens* ens) : e(ens), together(ens->cls.size() > 1 && threads > 1) {
         status.resize(e->cls.size());
+        pred.resize(e->cls.size());
         for (pisoc_ctx* ctx : e->cls) {
             info.emplace_back(ctx->batch);
-            if (audit_on(ctx)) together = false;
+            if (audit_on(ctx) || ctx->prm.guess == PISOC_GUESS_PREVIOUS || ctx->prm.capture)
+                together = false;
         }
         if (together && hipGetDevice(&dev) != hipSuccess) together = false;
     }
     void attempt(size_t c) noexcept {
         try {
+            pisoc_ctx* ctx = e->cls[c];
+            std::copy(ctx->pred_first, ctx->pred_first + PISOC_MAX_CORR, pred[c].first);
+            pred[c].later = ctx->pred_later;
             std::fill(info[c].begin(), info[c].end(), pisoc_step_info{});
-            status[c] = try_step(e->cls[c], info[c].data());
+            status[c] = try_step(ctx, info[c].data());
         } catch (...) {   // out of host memory
             status[c] = PISOC_ERR_HIP;
         }
@@ -1998,7 +2013,7 @@ struct EagerRound {
         };
         std::vector<std::thread> workers;
         try {
-            while (workers.size() + 1 < std::min(status.size(), kEnsThreads))
+            while (workers.size() + 1 < std::min(status.size(), threads))
                 workers.emplace_back([&]() noexcept {
                     if (hipSetDevice(dev) == hipSuccess) work();
                 });
@@ -2010,6 +2025,14 @@ struct EagerRound {
     pisoc_status result(size_t c) {
         if (!together) attempt(c);
         return status[c];
+    }
+    // The classes from c on were tried for a step that is not taken.
+    void drop_from(size_t c) {
+        for (; together && c < status.size(); ++c) {
+            pisoc_ctx* ctx = e->cls[c];
+            std::copy(pred[c].first, pred[c].first + PISOC_MAX_CORR, ctx->pred_first);
+            ctx->pred_later = pred[c].later;
+        }
     }
 };
 
@@ -2441,6 +2464,7 @@ pisoc_status pisoc_ens_step(pisoc_ens* e, int32_t n_steps, int32_t mode, pisoc_s
                 pisoc_ctx* ctx = e->cls[c];
                 const pisoc_status s = round.result(c);
                 if (s < 0) {
+                    round.drop_from(c + 1);
                     e->err = ctx->err;
                     return s;
                 }
