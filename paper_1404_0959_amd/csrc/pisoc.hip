@@ -1974,11 +1974,11 @@ constexpr size_t kEnsThreads = 4;
 
 struct EagerRound {
     pisoc_ens* e;
+    const size_t threads = std::min<size_t>(kEnsThreads, std::thread::hardware_concurrency());
     bool together;
     int dev = 0;
     std::vector<std::vector<pisoc_step_info>> info;   // of each class's members
     std::vector<pisoc_status> status;
-    size_t threads = std::min<size_t>(kEnsThreads, std::thread::hardware_concurrency());
     struct Pred {
         int first[PISOC_MAX_CORR], later;
     };
