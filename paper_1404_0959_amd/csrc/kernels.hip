@@ -3269,7 +3269,10 @@ __global__ void __launch_bounds__(kTX * kTY) k_tiled(Phys ph, DevState* st, K ke
 // heads two; loads past the chunk's last needed plane are clamped.
 // Bound: the planes' load latency with one 512-thread block (FP64) per CU; the
 // gathered kernels re-read each stencil through the caches with 64-wide
-// wavefronts, 35 % of whose lanes idle at n = 100.  us per launch in FP64, before
+// wavefronts, 35 % of whose lanes idle at n = 100.  SUBS: a batch's blocks march
+// further than a single grid's, and the sums (K::NR) go out per sub planes, the
+// march of a single grid, as in the CG kernel's flat form (15.0 ms for five steps of
+// 24 members of 32 to 64 cells a side with one sum per march and so).  us per launch in FP64, before
 // and now: momentum sweep 24.1 and 13.8 at 70^3, 42.7 and 28.9 at 100^3; a step's
 // field kernels in all 382 and 247, 700 and 511 (FP32 237 and 202, 378 and 369);
 // at 64^3, where the tiles' 8-plane minimum left 64 blocks, an FP64 step took 662
@@ -3277,8 +3280,9 @@ __global__ void __launch_bounds__(kTX * kTY) k_tiled(Phys ph, DevState* st, K ke
 // 136^3 2577 and 2001, 160^3 3806 and 2768, 200^3 7790 and 5223, FP32 1397 and 1390,
 // 1859 and 1779, 4499 and 3812 (per cell the 64 x 8 tiles' 192^3 step takes 2 % less
 // than the one of 200^3).
-template <typename T, class K, bool SEG>
-__global__ void __launch_bounds__(kFlatFieldThreads) k_flat(Phys ph, DevState* st, K kern) {
+template <typename T, class K, bool SEG, bool SUBS>
+__global__ void __launch_bounds__(kFlatFieldThreads) k_flat(Phys ph, DevState* st, K kern, int sub,
+                                                            int per, int chunks) {
     MEMBER(ph)
     extern __shared__ __align__(16) unsigned char flat_lds[];
     constexpr int NS = K::NS;
@@ -3415,6 +3419,15 @@ __global__ void __launch_bounds__(kFlatFieldThreads) k_flat(Phys ph, DevState* s
     prefetch(clampk(k0 + 3, k1 + 1), clampk(k0 + 1, k1 - 1));
     double acc[NRA];
     k.init(acc);
+    // SUBS: one partial per row block and chunk of sub planes (per = cz / sub of
+    // them in a march, chunks in a column)
+    int kend = k0 + sub;
+    unsigned slot = bp_.y + gridDim.y * (unsigned)(mem_ * chunks + bz_ * per);
+    auto total = [&] {
+        __shared__ double red[kMaxWaves * NRA];
+        const double t = block_reduce<NRA, K::MASK, true>(acc, red, block_waves());
+        if (tid < NRA) k.part[(size_t)tid * (gridDim.y * chunks * ph.batch) + slot] = t;
+    };
     for (int kk = k0; kk < k1; ++kk) {
         if (act) {
 #pragma unroll
@@ -3486,8 +3499,17 @@ __global__ void __launch_bounds__(kFlatFieldThreads) k_flat(Phys ph, DevState* s
         }
         cur = nxt;
         prefetch(clampk(kk + 4, k1 + 1), clampk(kk + 2, k1 - 1));
+        if constexpr (SUBS) {
+            if (kk + 1 == kend && kend < k1) {
+                total();
+                k.init(acc);
+                slot += gridDim.y;
+                kend += sub;
+            }
+        }
     }
-    if constexpr (K::NR > 0) block_partials<K::NR, K::MASK>(acc, k.part);
+    if constexpr (SUBS) total();
+    else if constexpr (K::NR > 0) block_partials<K::NR, K::MASK>(acc, k.part);
     if (MEMBER_FIRST()) k.first(st + mem_);
 }
 
@@ -4364,7 +4386,7 @@ __global__ void __launch_bounds__(kBlock) k_gather(Phys ph, DevState* st, K kern
 }
 
 // Launch of k_tiled (or, where TL has rows, k_flat) over the tiled launch TL;
-// returns its block count (the number of partials a reducing functor writes).
+// returns the number of partials a reducing functor writes.
 template <typename T, class K>
 static unsigned flat_launch(const Launch& TL, hipStream_t s, const Phys& ph, const DevState* st,
                             const K& k) {
@@ -4372,14 +4394,23 @@ static unsigned flat_launch(const Launch& TL, hipStream_t s, const Phys& ph, con
     pt.cz = TL.cz;
     pt.nz = TL.nz;
     const size_t rows = (size_t)K::NS * (TL.rows + 4) + (K::FACES ? 2 * TL.rows + 1 : 0);
+    const size_t pitch = ph.n > kFlatFieldMaxN ? seg_width(ph.n, (int)TL.grid.x) + 4 : ph.n;
+    auto run = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, TL.grid, TL.block, rows * pitch * sizeof(T), s, pt,
+                           const_cast<DevState*>(st), k, TL.sub, TL.cz / TL.sub,
+                           (ph.n + TL.sub - 1) / TL.sub);
+    };
     if (ph.n > kFlatFieldMaxN) {
-        const size_t lds = rows * (seg_width(ph.n, (int)TL.grid.x) + 4) * sizeof(T);
-        hipLaunchKernelGGL((k_flat<T, K, true>), TL.grid, TL.block, lds, s, pt,
-                           const_cast<DevState*>(st), k);
-    } else {
-        hipLaunchKernelGGL((k_flat<T, K, false>), TL.grid, TL.block, rows * ph.n * sizeof(T), s, pt,
-                           const_cast<DevState*>(st), k);
+        run(k_flat<T, K, true, false>);
+        return TL.nblocks;
     }
+    if constexpr (K::NR > 0) {
+        if (TL.sub < TL.cz) {
+            run(k_flat<T, K, false, true>);
+            return TL.nparts;
+        }
+    }
+    run(k_flat<T, K, false, false>);
     return TL.nblocks;
 }
 template <typename T, class K>
@@ -4434,7 +4465,7 @@ Launch make_tiled_launch(int n, int batch, int cz_tile) {
         if (!rows) return L;   // nblocks = 0: not available
         gy = (n + rows - 1) / rows;
         L.rows = (n + gy - 1) / gy;
-        want = kFlatFieldBlocks / batch;
+        want = kFlatFieldBlocks;
         least = 1;
         L.block = dim3((L.rows * n + 63) / 64 * 64, 1, 1);
     }
@@ -4442,10 +4473,17 @@ Launch make_tiled_launch(int n, int batch, int cz_tile) {
     nz = nz < 1 ? 1 : nz;
     int cz = (n + nz - 1) / nz;
     if (cz < least) cz = least;
-    if (cz_tile > 0) cz = cz_tile < n ? cz_tile : n;
+    nz = (n + cz - 1) / cz;
+    L.sub = cz;
+    if (L.rows && gx == 1 && batch > 1) {   // longer marches, whole chunks of the single grid's
+        const int most = std::max(1, kFlatFieldBlocks / (gy * batch));
+        cz = std::min(n, cz * ((nz + most - 1) / most));
+    }
+    if (cz_tile > 0 && cz_tile != cz) L.sub = cz = cz_tile < n ? cz_tile : n;
     nz = (n + cz - 1) / cz;
     L.grid = dim3(gx, gy, nz * batch);
     L.nblocks = L.grid.x * L.grid.y * L.grid.z;
+    L.nparts = gx * gy * ((n + L.sub - 1) / L.sub) * batch;
     L.cz = cz;
     L.nz = nz;
     return L;

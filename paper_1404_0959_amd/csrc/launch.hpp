@@ -19,8 +19,8 @@ struct Launch {
     int v = 0;          // CG kernel: cells per lane along x of the full-row form (0: tiles)
     int h = 0;          // and wavefronts per x-row
     int rows = 0;       // and x-rows per block of its flat form (0: another form)
-    int sub = 0;        // and planes per partial sum of a block (cz, or a divisor of it)
-    unsigned nparts = 0;   // and partial sums per column, all members
+    int sub = 0;        // planes per partial sum of a block (cz, or a divisor of it)
+    unsigned nparts = 0;   // partial sums per column, all members
     bool gathered = false;   // a fused pass on the gathered launch (k_gather)
     bool nt = false;    // and its once-read fields streamed past the caches (make_spmv_launch)
 };
@@ -41,15 +41,17 @@ Launch make_launch_shaped(int n, int batch, int bx, int cz);
 // from 128 on, marching over at least 8 planes; else from 40 on on flattened rows
 // (rows x-rows per block), whole ones up to 128 (flat_field_rows) and segments of
 // them (seg_width) beyond; below 40 nblocks is 0.  Blocks march
-// over exactly min(cz_tile, n) planes when cz_tile > 0 (a tuned choice).
+// over exactly min(cz_tile, n) planes when cz_tile > 0 (a tuned choice; the
+// default's own cz changes nothing).
 // Flattened rows: as many as fit 512 threads (256 registers a thread in FP64), at
 // least 4, so that the y halo is no larger than the block's own rows: n <= 128.
 // Below n = 40 the gathered kernels are as fast (the launch's latency is all).
-// z is cut for one block per CU over all members: a single grid of 70^3 takes
-// 3-plane marches, 16 members of 64^3 take whole columns (3-plane marches there
-// cost 18 % of a step, reading two halo planes for each of their own).  A
-// member's cells do not depend on the cut; sums over its blocks (mass, ||b||^2)
-// are then added in another order than a single grid's.
+// z is cut for one block per CU: a single grid of 70^3 takes 3-plane marches.  A
+// batch's blocks march over several of the single grid's chunks, for one block per
+// CU over all members (16 members of 64^3 take whole columns: 3-plane marches there
+// cost 18 % of a step, reading two halo planes for each of their own), and add
+// their sums up per chunk, so that a member's (mass, ||b||^2) are those of a run of
+// its own.
 constexpr int kFlatFieldRows = 4, kFlatFieldThreads = 512, kFlatFieldBlocks = 256;
 constexpr int kFlatFieldMinN = 40, kFlatFieldMaxN = kFlatFieldThreads / kFlatFieldRows;
 constexpr int flat_field_rows(int n) {

@@ -212,11 +212,11 @@ Layout make_layout(const pisoc_params* p, int batch) {
     Layout L{};
     const size_t N = (size_t)p->n * p->n * p->n * (size_t)batch;
     const size_t es = p->precision == PISOC_FP64 ? sizeof(double) : sizeof(float);
-    unsigned mb = std::max({make_launch(p->n, batch).nblocks, make_tiled_launch(p->n, batch).nblocks,
+    unsigned mb = std::max({make_launch(p->n, batch).nblocks, make_tiled_launch(p->n, batch).nparts,
                             make_spmv_launch(p->n, batch, (int)es).nparts});
     for (int c : {8, 16, 32}) {   // the chunks the autotuner may choose
         mb = std::max(mb, make_spmv_launch(p->n, batch, (int)es, c).nparts);
-        mb = std::max(mb, make_tiled_launch(p->n, batch, c).nblocks);
+        mb = std::max(mb, make_tiled_launch(p->n, batch, c).nparts);
     }
     for (auto [bx, cz] : shape_candidates(p->n))
         mb = std::max(mb, make_launch_shaped(p->n, batch, bx, cz).nblocks);
@@ -2733,7 +2733,7 @@ const char* pisoc_ens_last_error(const pisoc_ens* e) { return e ? e->err.c_str()
 static Layout helm_layout(int32_t n) {
     Layout L{};
     const size_t N = (size_t)n * n * n;
-    L.max_blocks = std::max({make_launch(n, 1).nblocks, make_tiled_launch(n, 1).nblocks,
+    L.max_blocks = std::max({make_launch(n, 1).nblocks, make_tiled_launch(n, 1).nparts,
                              make_spmv_launch(n, 1, 8).nparts});
     size_t off = 0;
     auto take = [&](size_t bytes) { size_t o = off; off = align_up(off + bytes); return o; };

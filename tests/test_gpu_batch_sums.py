@@ -1,0 +1,54 @@
+"""A member of an eager ensemble is bitwise the same case run alone: every sum over its
+cells (||b||^2 and ||r||^2 of a pressure solve, the gas and dust mass) is added up in
+the order of a run of its own, however many members share the launches and however
+far their blocks march along z.  Sizes from 40 to 127 run the field kernels on whole
+flattened rows; 66 and 75 leave a short last chunk of planes.
+
+One step in FP32: from the second on a first refinement round is cut at the iterations
+that the slowest member of its class needed in the step before, where a run of its
+own takes its own count.
+"""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def P():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_1404_0959_amd.pisoc as P
+    P.lib()
+    return P
+
+
+@pytest.mark.parametrize("precision,n,members", [
+    ("fp64", 40, 12), ("fp32", 48, 9), ("fp64", 64, 5), ("fp32", 66, 8), ("fp64", 75, 16),
+    ("fp64", 127, 3), ("fp64", 129, 3),
+])
+def test_members_sum_as_single_runs(P, precision, n, members):
+    from paper_1404_0959_amd.inputs import make_hit_case
+    cs = [make_hit_case(n, 90 + m, mach=0.5 if m % 2 else 0.2, stokes=(0.1,)) for m in range(members)]
+    kw = dict(p_tol=1e-7, cfl=0.5)
+    if precision == "fp32":
+        kw.update(precision=P.FP32_REFINED, inner_tol=1e-3)
+    ens = P.Ensemble(cs, **kw)
+    steps = 1 if precision == "fp32" else 2
+    st, infos = ens.step(steps, mode=P.ENS_EAGER)
+    assert st in (P.OK, P.WARN_DUST)
+    bits = P.FIELD_RHO | P.FIELD_U | P.FIELD_RHO_P
+    for m in (0, members - 1):
+        s = P.Solver.from_case(cs[m], **kw)
+        st, rec = s.step(steps)
+        assert st in (P.OK, P.WARN_DUST)
+        want = rec[-1]
+        for key in ("mass_gas", "mass_p", "pcg_relres", "pcg_iters", "dt", "courant", "courant_dust"):
+            assert infos[m][key] == want[key], (m, key)
+        a = {k: v.cpu().numpy() for k, v in ens.fields(m, bits).items()}
+        b = {k: v.cpu().numpy() for k, v in s.fields(bits).items()}
+        for k in a:
+            assert np.array_equal(a[k], b[k]), (m, k)
+        s.close()
+    ens.close()
