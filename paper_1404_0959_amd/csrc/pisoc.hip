@@ -2036,7 +2036,13 @@ struct EagerRound {
     }
 };
 
+// The host waits (sync_state) end with a word that a kernel stores, not with the
+// stream: when the last replay's kernels are done the runtime may not yet have
+// retired its launch, which still refers to the executable graph.  The class
+// streams are therefore synchronised before any executable is destroyed.
 void drop_graphs(pisoc_ens* e) {
+    for (pisoc_ctx* ctx : e->cls)
+        if (ctx->stream) (void)hipStreamSynchronize(ctx->stream);
     for (auto& pair : e->exec)
         for (auto& g : pair)
             if (g) {
@@ -2718,9 +2724,7 @@ pisoc_status pisoc_ens_autotune(pisoc_ens* e, const char* cache_path, int32_t fo
 
 void pisoc_ens_destroy(pisoc_ens* e) {
     if (!e) return;
-    for (pisoc_ctx* ctx : e->cls)
-        if (ctx && ctx->stream) (void)hipStreamSynchronize(ctx->stream);
-    drop_graphs(e);
+    drop_graphs(e);   // synchronises the class streams
     for (hipEvent_t ev : e->fork_join) (void)hipEventDestroy(ev);
     for (pisoc_ctx* ctx : e->cls) free_ctx(ctx);
     for (hipStream_t s : e->streams) (void)hipStreamDestroy(s);
