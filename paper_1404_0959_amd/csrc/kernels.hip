@@ -1151,8 +1151,8 @@ __global__ void __launch_bounds__(kBlock) k_pcg_spmv(
 }
 
 // Tiled form: a block of TX x NTY threads owns a TX x (NTY RPT) column tile
-// (n a multiple of 64) and marches along z.  Each of r, q, p_old, diag and w is read once per cell
-// from HBM: the x-y neighbours of the current plane come from LDS tiles (halo
+// (64 x 8 threads for n a multiple of 64, 16 x 16 for other multiples of 16) and
+// marches along z.  Each of r, q, p_old, diag and w is read once per cell from HBM: the x-y neighbours of the current plane come from LDS tiles (halo
 // 2 for w; halo 1 for the direction p, formed from r, q, p_old and diag at
 // the halo cells), the z neighbours from per-thread register queues.
 template <typename T, int RPT, int XM, int TX, int NTY>
@@ -4443,6 +4443,23 @@ Launch make_launch(int n, int batch) {
     return make_launch_shaped(n, batch, bx, (n + nz - 1) / nz);
 }
 
+// The cut of n planes (into chunks of at least 8) whose blocks cost least, columns
+// blocks to a chunk: rounds of one block per CU, each as long as its planes and its
+// halo's (kCutHalo).
+static int cut_by_rounds(int n, int columns) {
+    int best = 1;
+    long least = -1;
+    for (int nz = 1; nz <= n / 8; ++nz) {
+        const long cost = (long)((columns * nz + kFlatBlocks - 1) / kFlatBlocks) *
+                          ((n + nz - 1) / nz + kCutHalo);
+        if (least < 0 || cost < least) {
+            least = cost;
+            best = nz;
+        }
+    }
+    return best;
+}
+
 Launch make_tiled_launch(int n, int batch, int cz_tile) {
     Launch L{};
     int gx = 1, gy, want, least;
@@ -4469,7 +4486,7 @@ Launch make_tiled_launch(int n, int batch, int cz_tile) {
         least = 1;
         L.block = dim3((L.rows * n + 63) / 64 * 64, 1, 1);
     }
-    int nz = want / (gx * gy);
+    int nz = L.rows && n > kCutMinN ? cut_by_rounds(n, gx * gy) : want / (gx * gy);
     nz = nz < 1 ? 1 : nz;
     int cz = (n + nz - 1) / nz;
     if (cz < least) cz = least;
@@ -4511,15 +4528,15 @@ Launch make_spmv_launch(int n, int batch, int elem_bytes, int cz_tile) {
         return L;
     }
     const int TY = kTY * spmv_rows(elem_bytes);
-    if (n > kFlatBeforeTiles && n % kTX == 0 && n % TY == 0) {
-        const int gx = n / kTX, gy = n / TY;
-        int nz = kTiledBlocks / (gx * gy);
-        nz = nz < 1 ? 1 : nz;
+    const bool wide = n > kFlatBeforeTiles && n % kTX == 0 && n % TY == 0;
+    if (wide || (n > small_tiles_above(elem_bytes) && n % kSmallTX == 0)) {
+        const int gx = n / (wide ? kTX : kSmallTX), gy = n / (wide ? TY : kSmallTX);
+        int nz = wide ? std::max(1, kTiledBlocks / (gx * gy)) : kSmallChunks;
         int cz = (n + nz - 1) / nz;
         if (cz < 8) cz = 8;
         if (cz_tile > 0) cz = cz_tile < n ? cz_tile : n;
         nz = (n + cz - 1) / cz;
-        L.block = dim3(kTX, kTY, 1);
+        L.block = wide ? dim3(kTX, kTY, 1) : dim3(kSmallTX, kSmallTX, 1);
         L.grid = dim3(gx, gy, nz * batch);
         L.nblocks = L.grid.x * L.grid.y * L.grid.z;
         L.cz = L.sub = cz;
@@ -4531,7 +4548,7 @@ Launch make_spmv_launch(int n, int batch, int elem_bytes, int cz_tile) {
     if (rows < 2) return L;   // nblocks = 0: not available
     const int gy = (n + rows - 1) / rows;
     rows = (n + gy - 1) / gy;
-    int nz = (n > 256 ? 2 * kFlatBlocks : kFlatBlocks) / gy;
+    int nz = n > kCutMinN ? cut_by_rounds(n, gy) : kFlatBlocks / gy;
     nz = nz < 1 ? 1 : nz > n ? n : nz;
     int cz = (n + nz - 1) / nz;
     if (cz_tile > 0) cz = cz_tile < n ? cz_tile : n;
@@ -4790,7 +4807,10 @@ static void spmv_launch(const Launch& L, const Launch& TL, hipStream_t s, const 
         Phys pt = ph;
         pt.cz = TL.cz;
         pt.nz = TL.nz;
-        LAUNCH((k_pcg_spmv_tiled<T, spmv_rows(sizeof(T)), XM, kTX, kTY>), TL, s, pt, SPMV_ARGS);
+        if (TL.block.x == kSmallTX)
+            LAUNCH((k_pcg_spmv_tiled<T, 1, XM, kSmallTX, kSmallTX>), TL, s, pt, SPMV_ARGS);
+        else
+            LAUNCH((k_pcg_spmv_tiled<T, spmv_rows(sizeof(T)), XM, kTX, kTY>), TL, s, pt, SPMV_ARGS);
     } else {
         LAUNCH((k_pcg_spmv<T, XM>), L, s, ph, SPMV_ARGS);
     }

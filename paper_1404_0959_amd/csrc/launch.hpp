@@ -59,11 +59,17 @@ constexpr int flat_field_rows(int n) {
 }
 // Segments: the fewest per row of at most kSegMost columns, in whole 64-byte lines
 // of doubles, so 64 to 96 columns and 5 to 7 rows per 512 threads (whole rows of
-// 160 would leave 3 rows a y halo larger than themselves).  z is cut for
-// kSegBlocks blocks and marches of at least 8 planes, whatever the batch: half as
+// 160 would leave 3 rows a y halo larger than themselves).  Up to kCutMinN z is cut
+// for kSegBlocks blocks and marches of at least 8 planes, whatever the batch: half as
 // many blocks took 9 % longer for an FP64 step of 200^3 (6 % less at 136^3), twice
 // as many 1-2 % longer from 136^3 to 200^3, four times 3-7 %.
-constexpr int kSegBlocks = 512;
+// Beyond, a plane alone takes hundreds of blocks, and a count just past a multiple of
+// the CUs leaves most of them idle in the last round: cut_by_rounds, of 9 cuts into 1
+// to 11 chunks swept at 17 sizes and precisions from 264 to 500 within 3 % of the
+// fastest each time.  Field kernels of a step, ms, gathered, 512 blocks, now: FP32
+// 288^3 7.6, 6.9, 5.9; 336^3 13.6, 16.2, 11.4; 352^3 14.4, 18.0, 12.9; 400^3 24.2, 20.7,
+// 16.2; FP64 336^3 25.5, 23.7, 16.1; 400^3 45.1, 30.7, 23.9.
+constexpr int kSegBlocks = 512, kCutMinN = 256, kCutHalo = 4;
 constexpr int kSegMost = 96, kSegWidth = 64, kSegRows = 5;
 __host__ __device__ constexpr int seg_width(int n, int gx) { return ((n + gx - 1) / gx + 7) / 8 * 8; }
 Launch make_tiled_launch(int n, int batch = 1, int cz_tile = 0);
@@ -79,7 +85,16 @@ Launch make_tiled_launch(int n, int batch = 1, int cz_tile = 0);
 //   tile's y halo; in FP32 two measured no faster).  At 320 the flat form took
 //   643 against 549 us in FP64 (272 against 255 in FP32): three rows per block
 //   leave it a y halo as large as the tile; at 192 and below it is the faster.
-// * Every other n with flat_rows(n) >= 2: the flat form, rows x-rows per block.
+// * Other multiples of kSmallTX beyond small_tiles_above: tiles of kSmallTX x
+//   kSmallTX cells, one thread per column (block.x = kSmallTX), kSmallChunks chunks
+//   of z.  There two full rows are all that the flat form's LDS holds (FP64) or none
+//   (FP32, and FP64 from 385 on, where the gathered form would be left).  us per
+//   iteration in FP64, flat or gathered, tiles: 336^3 776, 745; 352^3 914, 871; 368^3
+//   1019, 1017; 400^3 2367, 1266; 480^3 3886, 2255; 624^3 8999, 4832; in FP32 528^3
+//   2779, 2099; 624^3 3960, 3392, but 352^3 398, 622.  Of 1 to 12 chunks 4 is within
+//   4 % of the fastest at 19 sizes.
+// * Every other n with flat_rows(n) >= 2 (FP64 up to 384, FP32 up to 512): the flat
+//   form, rows x-rows per block.
 // nblocks is 0 when none is available.  Tiles march over at least 8 planes, or
 // like the flat form's single grids over exactly min(cz_tile, n) when cz_tile > 0
 // (a tuned choice; the full-row form ignores it).
@@ -92,14 +107,18 @@ Launch make_tiled_launch(int n, int batch = 1, int cz_tile = 0);
 constexpr double kMallBytes = 256.0 * 1024 * 1024;
 constexpr int spmv_rows(int elem_bytes) { return elem_bytes == 8 ? 2 : 1; }
 constexpr int kFlatBeforeTiles = 256;
+constexpr int kSmallTX = 16, kSmallChunks = 4;
+constexpr int small_tiles_above(int elem_bytes) { return elem_bytes == 8 ? 320 : 512; }
 // Rows per block of the flat form: as many as fit 512 threads up to n = 64, 768
 // up to 100, 1024 beyond (larger blocks read less halo; smaller ones spread the
 // same planes over more CUs and shorter marches), but at least 8 blocks per plane
 // up to n = 40, where whole planes would leave CUs idle.  z is then cut for one
-// block per CU (kFlatBlocks, two from n = 257 on), so that no block waits for
-// another to end and the launch's head totals few partials: of the shapes
-// swept at 24 sizes from 16 to 336 in both precisions the rule's is within
-// 10 % of the fastest, and half or twice as many blocks take 5-40 % longer.
+// block per CU (kFlatBlocks), so that no block waits for another to end and the
+// launch's head totals few partials: of the shapes swept from 16 to 256 in both
+// precisions the rule's is within 10 % of the fastest, and half or twice as many
+// blocks take 5-40 % longer.  From n = 257 on by cut_by_rounds, of 11 cuts swept at 18
+// sizes within 5 % of the fastest (FP64 330^3 757 us per iteration, 360^3 1196 with
+// two blocks per CU and 975 now; FP32 400^3 632 and 552).
 // A batch has blocks enough without short marches, and with the single grid's
 // most of a block's time is its head and halo planes: its blocks march over
 // several chunks, for at most kFlatBatchBlocks in all (the partial sums stay per
