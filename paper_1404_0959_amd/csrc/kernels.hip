@@ -14,8 +14,9 @@ namespace pisoc {
 
 // The member of this block (blocks of member m have blockIdx.z in
 // [m nz, (m+1) nz)), its z-block and its first cell.
-#define MEMBER(ph)                                                           \
-    const BlockXYZ bp_ = block_xyz();                                        \
+#define MEMBER(ph) MEMBER_AT(ph, block_xyz())
+#define MEMBER_AT(ph, xyz)                                                   \
+    const BlockXYZ bp_ = xyz;                                                \
     const int mem_ = bp_.z / (ph).nz;                                        \
     const int bz_ = bp_.z - mem_ * (ph).nz;                                  \
     const size_t base_ = (size_t)mem_ * (ph).N;                              \
@@ -1163,7 +1164,8 @@ __global__ void __launch_bounds__(TX * NTY) k_pcg_spmv_tiled(
     T* __restrict__ q, T* __restrict__ x, const double* part_in, unsigned nb_in, double* part_out,
     int fresh, int maxit, int xzero) {
     constexpr bool UPD = XM > 0, XE = XM == 2;
-    MEMBER(ph)
+    constexpr bool REST = TX != kTX;   // the renumbering of a remainder (flat_bid)
+    MEMBER_AT(ph, block_xyz<REST>())
     const CgIn<XM> in = cg_load<XM>(ph, (st + mem_)->pcg, mem_, part_in, nb_in);
     if (k > in.it_stop) return;   // see k_pcg_spmv
     const CgHead h = cg_head<XM>(in, (st + mem_)->pcg, MEMBER_FIRST(), k, fresh, maxit);
@@ -1378,7 +1380,7 @@ __global__ void __launch_bounds__(TX * NTY) k_pcg_spmv_tiled(
             }
         }
     }
-    block_partials<CG_COLS, 0u, true>(acc, part_out);
+    block_partials<CG_COLS, 0u, true, REST>(acc, part_out);
 }
 
 // Row form for n = 64 V H: a block of kRowWaves wavefronts owns kRowWaves / H

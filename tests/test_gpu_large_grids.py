@@ -22,7 +22,7 @@ def P():
     return P
 
 
-@pytest.mark.parametrize("n", [257, 300, 320, 336, 400])
+@pytest.mark.parametrize("n", [257, 300, 320, 336, 400, 448])
 def test_cg_matches_oracle(P, ora, n):
     """The first iterations of the FP64 solve (one and two x updates per launch, the
     last one at the cap) against the oracle's, to 1e-12 of the solution as for the
