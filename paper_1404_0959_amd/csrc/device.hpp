@@ -386,6 +386,45 @@ __device__ inline void block_partials(double (&v)[NV], double* part) {
     if (c < NV) part[(size_t)c * num_blocks() + flat_bid<REST>()] = t;
 }
 
+// The same per chunk of a march (a batch's block totals each chunk that a single
+// grid's block marches over): a wave leaves its totals of a chunk in LDS, and the
+// waves are added after the march, in block_reduce's order, so that a chunk costs
+// neither a barrier nor a chain of LDS reads.  us of an FP64 step with a block's total
+// per chunk, so: 64 members of 16^3 1396 and 1226, 24 of 32^3 1363 and 1240.
+__host__ __device__ constexpr size_t lds_after(size_t bytes) { return (bytes + 7) / 8 * 8; }
+constexpr size_t chunk_sums_lds(int chunks, int threads, int columns) {
+    return sizeof(double) * (size_t)chunks * (threads / 64) * columns;
+}
+template <int NV, unsigned MAXMASK>
+struct ChunkSums {
+    double* lds;    // chunk_sums_lds of them
+    int held = 0;   // chunks added
+    __device__ explicit ChunkSums(void* at) : lds(reinterpret_cast<double*>(at)) {}
+    __device__ void add(double (&v)[NV]) {
+        wave_reduce_all<NV, MAXMASK>(v);
+        const int tid = flat_tid();
+        if ((tid & 63) == 63)
+#pragma unroll
+            for (int c = 0; c < NV; ++c) lds[(held * block_waves() + (tid >> 6)) * NV + c] = v[c];
+        ++held;
+    }
+    // chunk h to slot + h step of each column, the columns `column` apart
+    __device__ void store(double* part, size_t column, size_t slot, size_t step) const {
+        const int waves = block_waves();
+        lds_barrier();
+        for (int i = flat_tid(); i < held * NV; i += (int)blockDim.x) {
+            const int h = i / NV, c = i - h * NV;
+            const double* w0 = lds + h * waves * NV + c;
+            double t = w0[0];
+            for (int w = 1; w < waves; ++w) {
+                const double x = w0[w * NV];
+                t = (MAXMASK >> c) & 1u ? combine<true>(t, x) : t + x;
+            }
+            part[c * column + slot + h * step] = t;
+        }
+    }
+};
+
 // Partials of an earlier kernel on their way to this thread: its first one of
 // each of NV columns (nbt apart, count nb from `first` on).  Loading them ahead
 // of the totals (reduce_loaded) lets other loads be issued in between.

@@ -1741,14 +1741,11 @@ __global__ void __launch_bounds__(MT, 4) k_pcg_spmv_flat(
     T pc = dirf(zc, oc);
     T kzm = (T(9) * (wm1 + w0) - (wmm + wp1)) * T(0.0625);
     double acc[CG_COLS] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
-    // partials: one slot per row block and chunk of sub planes (per = cz / sub of
-    // them in a march, chunks in a column)
-    unsigned slot = bp_.y + gridDim.y * (unsigned)(mem_ * chunks + bz_ * per);
-    auto total = [&] {
-        __shared__ double red[kMaxWaves * CG_COLS];
-        const double t = block_reduce<CG_COLS, 0u, true>(acc, red, block_waves());
-        if (tid < CG_COLS) part_out[(size_t)tid * (gridDim.y * chunks * ph.batch) + slot] = t;
-    };
+    // partials: one slot per row block and chunk of sub planes (per of them in a march,
+    // chunks in a column); SUBS: a march has several
+    const unsigned column = gridDim.y * chunks * ph.batch;
+    const unsigned slot = bp_.y + gridDim.y * (unsigned)(mem_ * chunks + bz_ * per);
+    ChunkSums<CG_COLS, 0u> sums(flat_lds + flat_cg_lds(n, R, sizeof(T)));
     int kend = k0 + sub;
     for (int kk = k0; kk < k1; ++kk) {
         const T wp2 = wp2n;
@@ -1825,15 +1822,20 @@ __global__ void __launch_bounds__(MT, 4) k_pcg_spmv_flat(
             xc = xn1;
             o2c = o2n1;
         }
-        if (SUBS && kk + 1 == kend && kend < k1) {
-            total();
+        if (SUBS && (kk + 1 == kend || kk + 1 == k1)) {
+            sums.add(acc);
 #pragma unroll
             for (int c = 0; c < CG_COLS; ++c) acc[c] = 0.0;
-            slot += gridDim.y;
             kend += sub;
         }
     }
-    total();
+    if (SUBS) {
+        sums.store(part_out, column, slot, gridDim.y);
+    } else {
+        __shared__ double red[kMaxWaves * CG_COLS];
+        const double t = block_reduce<CG_COLS, 0u, true>(acc, red, block_waves());
+        if (tid < CG_COLS) part_out[(size_t)tid * column + slot] = t;
+    }
 }
 
 // ---- CG preconditioned by a Chebyshev polynomial (stand-alone solve) ----
@@ -3421,15 +3423,9 @@ __global__ void __launch_bounds__(kFlatFieldThreads) k_flat(Phys ph, DevState* s
     prefetch(clampk(k0 + 3, k1 + 1), clampk(k0 + 1, k1 - 1));
     double acc[NRA];
     k.init(acc);
-    // SUBS: one partial per row block and chunk of sub planes (per = cz / sub of
-    // them in a march, chunks in a column)
+    // SUBS: as in the CG kernel
     int kend = k0 + sub;
-    unsigned slot = bp_.y + gridDim.y * (unsigned)(mem_ * chunks + bz_ * per);
-    auto total = [&] {
-        __shared__ double red[kMaxWaves * NRA];
-        const double t = block_reduce<NRA, K::MASK, true>(acc, red, block_waves());
-        if (tid < NRA) k.part[(size_t)tid * (gridDim.y * chunks * ph.batch) + slot] = t;
-    };
+    ChunkSums<NRA, K::MASK> sums(flat_lds + lds_after((NS * us + (FACES ? 2 * R + 1 : 0) * pw) * sizeof(T)));
     for (int kk = k0; kk < k1; ++kk) {
         if (act) {
 #pragma unroll
@@ -3481,6 +3477,14 @@ __global__ void __launch_bounds__(kFlatFieldThreads) k_flat(Phys ph, DevState* s
         }
         lds_barrier();
         if (act) k.cell(col + nn * (size_t)kk, v, fp, fm, cur, acc);
+        // before the next loads go out: they would be waited for here
+        if constexpr (SUBS) {
+            if (kk + 1 == kend || kk + 1 == k1) {
+                sums.add(acc);
+                k.init(acc);
+                kend += sub;
+            }
+        }
         // advance the queues with the values loaded a plane ago, then load the
         // queue heads at kk + 4 and the values of plane kk + 2
 #pragma unroll
@@ -3501,17 +3505,12 @@ __global__ void __launch_bounds__(kFlatFieldThreads) k_flat(Phys ph, DevState* s
         }
         cur = nxt;
         prefetch(clampk(kk + 4, k1 + 1), clampk(kk + 2, k1 - 1));
-        if constexpr (SUBS) {
-            if (kk + 1 == kend && kend < k1) {
-                total();
-                k.init(acc);
-                slot += gridDim.y;
-                kend += sub;
-            }
-        }
     }
-    if constexpr (SUBS) total();
-    else if constexpr (K::NR > 0) block_partials<K::NR, K::MASK>(acc, k.part);
+    if constexpr (SUBS)
+        sums.store(k.part, (size_t)gridDim.y * chunks * ph.batch,
+                   bp_.y + gridDim.y * (size_t)(mem_ * chunks + bz_ * per), gridDim.y);
+    else if constexpr (K::NR > 0)
+        block_partials<K::NR, K::MASK>(acc, k.part);
     if (MEMBER_FIRST()) k.first(st + mem_);
 }
 
@@ -4397,9 +4396,10 @@ static unsigned flat_launch(const Launch& TL, hipStream_t s, const Phys& ph, con
     pt.nz = TL.nz;
     const size_t rows = (size_t)K::NS * (TL.rows + 4) + (K::FACES ? 2 * TL.rows + 1 : 0);
     const size_t pitch = ph.n > kFlatFieldMaxN ? seg_width(ph.n, (int)TL.grid.x) + 4 : ph.n;
-    auto run = [&](auto kernel) {
-        hipLaunchKernelGGL(kernel, TL.grid, TL.block, rows * pitch * sizeof(T), s, pt,
-                           const_cast<DevState*>(st), k, TL.sub, TL.cz / TL.sub,
+    const int per = (TL.cz + TL.sub - 1) / TL.sub;
+    auto run = [&](auto kernel, size_t sums = 0) {
+        hipLaunchKernelGGL(kernel, TL.grid, TL.block, lds_after(rows * pitch * sizeof(T)) + sums, s,
+                           pt, const_cast<DevState*>(st), k, TL.sub, per,
                            (ph.n + TL.sub - 1) / TL.sub);
     };
     if (ph.n > kFlatFieldMaxN) {
@@ -4408,7 +4408,7 @@ static unsigned flat_launch(const Launch& TL, hipStream_t s, const Phys& ph, con
     }
     if constexpr (K::NR > 0) {
         if (TL.sub < TL.cz) {
-            run(k_flat<T, K, false, true>);
+            run(k_flat<T, K, false, true>, chunk_sums_lds(per, (int)TL.block.x, K::NR));
             return TL.nparts;
         }
     }
@@ -4445,18 +4445,20 @@ Launch make_launch(int n, int batch) {
     return make_launch_shaped(n, batch, bx, (n + nz - 1) / nz);
 }
 
-// The cut of n planes (into chunks of at least 8) whose blocks cost least, columns
-// blocks to a chunk: rounds of one block per CU, each as long as its planes and its
-// halo's (kCutHalo).
-static int cut_by_rounds(int n, int columns) {
-    int best = 1;
-    long least = -1;
-    for (int nz = 1; nz <= n / 8; ++nz) {
-        const long cost = (long)((columns * nz + kFlatBlocks - 1) / kFlatBlocks) *
-                          ((n + nz - 1) / nz + kCutHalo);
-        if (least < 0 || cost < least) {
-            least = cost;
-            best = nz;
+// Planes per block of the cut of n planes that costs least, columns blocks to a
+// chunk: rounds of one block per CU, each as long as its planes and its halo's
+// (kCutHalo).  At least `least` planes, a whole number of units; the shorter march
+// where two cuts cost the same (its rounds overlap).
+static int cut_by_rounds(int n, int columns, int unit, int least) {
+    int best = n;
+    long cost = -1;
+    for (int nz = 1; nz <= n / least; ++nz) {
+        const int cz = std::min(n, ((n + nz - 1) / nz + unit - 1) / unit * unit);
+        const long blocks = (long)columns * ((n + cz - 1) / cz);
+        const long c = (blocks + kFlatBlocks - 1) / kFlatBlocks * (cz + kCutHalo);
+        if (cost < 0 || c <= cost) {
+            cost = c;
+            best = cz;
         }
     }
     return best;
@@ -4488,16 +4490,12 @@ Launch make_tiled_launch(int n, int batch, int cz_tile) {
         least = 1;
         L.block = dim3((L.rows * n + 63) / 64 * 64, 1, 1);
     }
-    int nz = L.rows && n > kCutMinN ? cut_by_rounds(n, gx * gy) : want / (gx * gy);
-    nz = nz < 1 ? 1 : nz;
-    int cz = (n + nz - 1) / nz;
-    if (cz < least) cz = least;
-    nz = (n + cz - 1) / cz;
+    int nz = std::max(1, want / (gx * gy));
+    int cz = std::max(least, (n + nz - 1) / nz);
+    if (L.rows && n > kCutMinN) cz = cut_by_rounds(n, gx * gy, 1, least);
     L.sub = cz;
-    if (L.rows && gx == 1 && batch > 1) {   // longer marches, whole chunks of the single grid's
-        const int most = std::max(1, kFlatFieldBlocks / (gy * batch));
-        cz = std::min(n, cz * ((nz + most - 1) / most));
-    }
+    if (L.rows && gx == 1 && batch > 1)   // longer marches, whole chunks of the single grid's
+        cz = cut_by_rounds(n, gy * batch, cz, cz);
     if (cz_tile > 0 && cz_tile != cz) L.sub = cz = cz_tile < n ? cz_tile : n;
     nz = (n + cz - 1) / cz;
     L.grid = dim3(gx, gy, nz * batch);
@@ -4550,9 +4548,9 @@ Launch make_spmv_launch(int n, int batch, int elem_bytes, int cz_tile) {
     if (rows < 2) return L;   // nblocks = 0: not available
     const int gy = (n + rows - 1) / rows;
     rows = (n + gy - 1) / gy;
-    int nz = n > kCutMinN ? cut_by_rounds(n, gy) : kFlatBlocks / gy;
+    int nz = kFlatBlocks / gy;
     nz = nz < 1 ? 1 : nz > n ? n : nz;
-    int cz = (n + nz - 1) / nz;
+    int cz = n > kCutMinN ? cut_by_rounds(n, gy, 1, 8) : (n + nz - 1) / nz;
     if (cz_tile > 0) cz = cz_tile < n ? cz_tile : n;
     nz = (n + cz - 1) / cz;
     L.rows = rows;
@@ -4560,8 +4558,12 @@ Launch make_spmv_launch(int n, int batch, int elem_bytes, int cz_tile) {
     L.sub = cz;
     L.nparts = gy * nz * batch;
     if (batch > 1) {   // longer marches, whole chunks of the single grid's
-        const int most = std::max(1, kFlatBatchBlocks / (gy * batch));
-        cz *= (nz + most - 1) / most;
+        const int waves = (int)L.block.x / 64;
+        const int all = waves > 8 ? kFlatBatchBlocks : std::min(kFlatBatchBlocks, kFlatBatchWaves / waves);
+        const int most = std::max(1, all / (gy * batch));
+        const size_t one = chunk_sums_lds(1, (int)L.block.x, kCgCols);
+        const int fit = (int)((kFlatLdsAll - flat_cg_lds(n, rows, elem_bytes)) / one);
+        cz *= std::min(fit, (nz + most - 1) / most);
         nz = (n + cz - 1) / cz;
     }
     L.grid = dim3(1, gy, nz * batch);
@@ -4786,11 +4788,13 @@ static void spmv_launch(const Launch& L, const Launch& TL, hipStream_t s, const 
         Phys pt = ph;
         pt.cz = TL.cz;
         pt.nz = TL.nz;
-        const size_t lds = flat_cg_lds(ph.n, TL.rows, sizeof(T));
+        const int per = (TL.cz + TL.sub - 1) / TL.sub;
+        const size_t lds = flat_cg_lds(ph.n, TL.rows, sizeof(T)) +
+                           (TL.sub < TL.cz ? chunk_sums_lds(per, (int)TL.block.x, CG_COLS) : 0);
         const bool one = 4u * ph.n <= TL.block.x;
 #define FLAT(HW, MT, SUBS)                                                                         \
     hipLaunchKernelGGL((k_pcg_spmv_flat<T, XM, HW, MT, SUBS>), TL.grid, TL.block, lds, s, pt,      \
-                       SPMV_ARGS, TL.sub, TL.cz / TL.sub, (ph.n + TL.sub - 1) / TL.sub)
+                       SPMV_ARGS, TL.sub, per, (ph.n + TL.sub - 1) / TL.sub)
         auto run = [&](auto subs) {
             if (TL.block.x <= 512) {
                 if (one) FLAT(1, 512, subs.value);

@@ -47,11 +47,12 @@ Launch make_launch_shaped(int n, int batch, int bx, int cz);
 // least 4, so that the y halo is no larger than the block's own rows: n <= 128.
 // Below n = 40 the gathered kernels are as fast (the launch's latency is all).
 // z is cut for one block per CU: a single grid of 70^3 takes 3-plane marches.  A
-// batch's blocks march over several of the single grid's chunks, for one block per
-// CU over all members (16 members of 64^3 take whole columns: 3-plane marches there
-// cost 18 % of a step, reading two halo planes for each of their own), and add
-// their sums up per chunk, so that a member's (mass, ||b||^2) are those of a run of
-// its own.
+// batch's blocks march over several of the single grid's chunks (16 members of 64^3
+// in 3-plane marches took 18 % longer, reading two halo planes for each of their
+// own), as cut_by_rounds has it, and add their sums up per chunk, so that a member's
+// (mass, ||b||^2) are those of a run of its own.  ms of a step cut for one block per
+// CU over all members, so: FP32 12 members of 64^3 2.10 and 1.92, 24 3.91 and 3.50; FP64
+// 24 of 64^3 6.52 and 6.21, 8 of 100^3 8.10 and 7.27.
 constexpr int kFlatFieldRows = 4, kFlatFieldThreads = 512, kFlatFieldBlocks = 256;
 constexpr int kFlatFieldMinN = 40, kFlatFieldMaxN = kFlatFieldThreads / kFlatFieldRows;
 constexpr int flat_field_rows(int n) {
@@ -111,8 +112,12 @@ constexpr int kSmallTX = 16, kSmallChunks = 4;
 constexpr int small_tiles_above(int elem_bytes) { return elem_bytes == 8 ? 320 : 512; }
 // Rows per block of the flat form: as many as fit 512 threads up to n = 64, 768
 // up to 100, 1024 beyond (larger blocks read less halo; smaller ones spread the
-// same planes over more CUs and shorter marches), but at least 8 blocks per plane
-// up to n = 40, where whole planes would leave CUs idle.  z is then cut for one
+// same planes over more CUs and shorter marches), but up to n = 40 in
+// about 8 blocks per plane, of at least 8 rows, where whole planes would leave CUs
+// idle and a few rows make a batch of many blocks.  ms of a step with 8 blocks of 2 to
+// 4 rows, with 8 rows: 64 members of 16^3 1.40 and 0.95 (1.25 on 16 x 16 tiles), 24 of
+// 32^3 1.36 and 1.23 (1.35); us per iteration of one grid of 16^3 9.1 and 8.5, of 32^3
+// 9.5 and 9.5.  z is then cut for one
 // block per CU (kFlatBlocks), so that no block waits for another to end and the
 // launch's head totals few partials: of the shapes swept from 16 to 256 in both
 // precisions the rule's is within 10 % of the fastest, and half or twice as many
@@ -121,21 +126,24 @@ constexpr int small_tiles_above(int elem_bytes) { return elem_bytes == 8 ? 320 :
 // two blocks per CU and 975 now; FP32 400^3 632 and 552).
 // A batch has blocks enough without short marches, and with the single grid's
 // most of a block's time is its head and halo planes: its blocks march over
-// several chunks, for at most kFlatBatchBlocks in all (the partial sums stay per
-// chunk, so a member's are those of a run of its own).  FP32, 12 members of 32^3
-// with 6 of 48^3 and 6 of 64^3: a step of all took 3.46 ms with the single
-// grid's marches, 3.20 so; a quarter, half or twice as many blocks 3.41, 3.30 and
-// 3.40, and 2 members of 64^3 are the same either way.
+// several chunks (the partial sums stay per chunk, so a member's are those of a run
+// of its own), for at most kFlatBatchBlocks in all, and up to 512 threads for no
+// more waves than are resident at once (kFlatBatchWaves: 16 per CU, four per SIMD).
+// Captured FP32 steps, ms, with at most 1024 blocks, so: 12 members of 48^3 1.57 and
+// 1.44 (16 x 16 tiles 1.43), 10 of 52^3 1.53 and 1.41, 8 of 56^3 1.49 and 1.36, 6 of 64^3
+// 1.33 both; 24 of 32^3 0.94, with half as many blocks 1.04.  Wider blocks, one per
+// CU, gain from 256 blocks at some sizes (5 of 80^3 2.23 and 2.01) and lose at others
+// (6 of 120^3 9.13 and 10.67 in FP64).
 // The block's LDS (two plane sets of R + 4 rows of w and R + 2 of p) stays
 // within kFlatLds beside the reduction's.
-constexpr int kFlatBlocks = 256, kFlatBatchBlocks = 1024;
-constexpr size_t kFlatLds = 60 * 1024;
+constexpr int kFlatBlocks = 256, kFlatBatchBlocks = 1024, kFlatBatchWaves = 4096;
+constexpr size_t kFlatLds = 60 * 1024, kFlatLdsAll = 62 * 1024;   // without, with a batch's chunk sums
 constexpr size_t flat_cg_lds(int n, int rows, int elem_bytes) {
     return (size_t)2 * (2 * rows + 6) * n * elem_bytes;
 }
 constexpr int flat_rows(int n, int elem_bytes) {
     int r = (n <= 64 ? 512 : n <= 100 ? 768 : 1024) / n;
-    if (n <= 40) r = n <= 16 ? 2 : (n + 7) / 8;
+    if (n <= 40) r = n <= 32 ? 8 : (n + 7) / 8;
     while (r >= 2 && flat_cg_lds(n, r, elem_bytes) > kFlatLds) --r;
     return r;
 }

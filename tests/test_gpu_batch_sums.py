@@ -2,7 +2,8 @@
 cells (||b||^2 and ||r||^2 of a pressure solve, the gas and dust mass) is added up in
 the order of a run of its own, however many members share the launches and however
 far their blocks march along z.  Sizes from 40 to 127 run the field kernels on whole
-flattened rows; 66 and 75 leave a short last chunk of planes.
+flattened rows; 66 and 75 leave a short last chunk of planes, 31 a last block of rows
+that is smaller than the others, and in 14 members of 64^3 a march takes several chunks.
 
 One step in FP32: from the second on a first refinement round is cut at the iterations
 that the slowest member of its class needed in the step before, where a run of its
@@ -26,7 +27,7 @@ def P():
 
 @pytest.mark.parametrize("precision,n,members", [
     ("fp64", 40, 12), ("fp32", 48, 9), ("fp64", 64, 5), ("fp32", 66, 8), ("fp64", 75, 16),
-    ("fp64", 127, 3), ("fp64", 129, 3),
+    ("fp64", 127, 3), ("fp64", 129, 3), ("fp64", 8, 40), ("fp64", 16, 40), ("fp32", 31, 20), ("fp64", 64, 14),
 ])
 def test_members_sum_as_single_runs(P, precision, n, members):
     from paper_1404_0959_amd.inputs import make_hit_case
