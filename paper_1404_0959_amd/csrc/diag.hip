@@ -315,7 +315,9 @@ __global__ void __launch_bounds__(1024) k_spectrum_total(const double* __restric
 // fields then went through memory.  256^3: Q 0.17 ms instead of 0.52 (3.1 TB/s of
 // its four words), the filtered statistics 0.48 instead of 1.55.  Bound: staging,
 // barrier and arithmetic in turn, with two to three blocks per CU to overlap them.
-constexpr int kMX = 64, kMY = 8, kMThreads = kMX * kMY, kMBlocks = 1024;
+// A small grid is the launch and one march: us per call with 4 planes, so: Q 54 and
+// 50, statistics 64 and 56 from 8^3 to 32^3 (48^3 53 and 52, 65 and 62).
+constexpr int kMX = 64, kMY = 8, kMThreads = kMX * kMY, kMBlocks = 1024, kMCus = 256;
 constexpr int kSY = 4;   // rows of the kernels that keep a ring of planes
 struct March {
     dim3 grid;
@@ -327,7 +329,10 @@ March make_march(int n, int rows = kMY) {
     const int gx = (n + kMX - 1) / kMX, gy = (n + rows - 1) / rows;
     int nz = kMBlocks * (kMY / rows) / (gx * gy);
     nz = nz < 1 ? 1 : nz;
-    m.cz = std::max((n + nz - 1) / nz, std::min(n, 4));
+    // shorter marches than 4 planes only while the blocks are no more than the CUs
+    int least = 1;
+    while (least < 4 && gx * gy * ((n + least - 1) / least) > kMCus) ++least;
+    m.cz = std::max((n + nz - 1) / nz, std::min(n, least));
     nz = (n + m.cz - 1) / m.cz;
     m.grid = dim3(gx, gy, nz);
     m.blocks = (unsigned)gx * gy * nz;
