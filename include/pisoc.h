@@ -357,9 +357,11 @@ typedef struct {
     int32_t rounds;                     /* ... FP64 refinement rounds (FP32_REFINED) */
     int32_t guess_mask;                 /* ... bit c set: corrector c's solve starts from
                                            the learned guess */
-    int32_t cg_cells_z;                 /* planes per block of the CG kernel's z-march
-                                           (0: its gathered form) */
-    int32_t tiled_cells_z;              /* ... of the other tiled z-marches (0: none) */
+    int32_t cg_cells_z;                 /* planes per partial sum of the CG kernel's
+                                           z-march (0: its gathered form); a block of
+                                           a batch marches over a whole number of them */
+    int32_t tiled_cells_z;              /* planes per block of the other z-marches
+                                           (0: none) */
 } pisoc_ens_class;
 
 /* Workspace for the ensemble (0 if the members are invalid); 256-byte aligned. */

@@ -193,8 +193,9 @@ __global__ void __launch_bounds__(kFftItems) k_fft_y(cplx* __restrict__ f, const
         for (int r = 0; r < 4; ++r) line[(size_t)(base + r * q) * Hp] = a[r];
 }
 
-// floor(sqrt(v)) for 0 <= v <= 3 512^2: the hardware root is within 1 ulp (6e-5
-// below 1024), and the roots of r^2 - 1 and r^2 lie 1 / (2 r) >= 5.6e-4 apart.
+// floor(sqrt(v)) for 0 <= v <= 887 888 (the last shell's end at n = 1024): the
+// hardware root is within 1 ulp (6e-5 below 1024), and the roots of r^2 - 1 and r^2 lie
+// 1 / (2 r) >= 5.6e-4 apart.
 __device__ inline int isqrt(int v) { return (int)(__builtin_amdgcn_sqrtf((float)v) + 1.5e-4f); }
 
 // z pass and binning: tiles of L lines at consecutive kx and one ky, dealt to the

@@ -3599,98 +3599,6 @@ struct TiledMomSource : TiledBase<T> {
 };
 
 template <typename T>
-struct TiledCorrFlux : TiledBase<T> {
-    static constexpr int NS = 3;          // w, p0, x
-    const T* sf[3];
-    const T* phiH;
-    T *phik, *pt;
-    double* snap_x;
-    T A, inv_h;
-    struct Pts { T h[3]; };
-    __device__ void member(const Phys& ph, const DevState*) {
-        this->NT = ph.NT;
-        A = (T)ph.A;
-        inv_h = (T)ph.inv_h;
-    }
-    __device__ Pts load(size_t P) const {
-        return {{stream_ld(phiH + P), stream_ld(phiH + this->NT + P),
-                 stream_ld(phiH + 2 * this->NT + P)}};
-    }
-    __device__ void cell(size_t P, const T (&v)[3][13], const T (&)[3], const T (&)[3],
-                         const Pts& p, double*) const {
-        T p0n[3], xn[3];
-#pragma unroll
-        for (int d = 0; d < 3; ++d) {
-            p0n[d] = v[1][3 + 4 * d];   // +1 along d
-            xn[d] = v[2][3 + 4 * d];
-        }
-        T pP, fk[3];
-        corr_flux_cell(v[0], v[1][0], v[2][0], p0n, xn, p.h, A, inv_h, pP, fk);
-        stream_st(pt + P, pP);
-#pragma unroll
-        for (int d = 0; d < 3; ++d) stream_st(phik + (d * this->NT + P), fk[d]);
-        if (snap_x) snap_x[P] = (double)v[2][0];
-    }
-};
-
-template <typename T, bool LAST>
-struct TiledCorrUpdate : TiledBase<T> {
-    static constexpr int NS = 1;          // p
-    static constexpr bool FACES = true;   // phi_k
-    static constexpr int NR = LAST ? 3 : 0;
-    static constexpr unsigned MASK = 4u;  // column 2 is a maximum
-    const T* sf[1];
-    const T *rn, *hbya, *aP;
-    T *rk, *u;
-    T dt, inv_V, inv_h;
-    double rref;
-    const double *bc, *rm1;   // BDF2: the coefficients and rho at t^{n-1}
-    double inv_Vd;
-    struct Pts { T hb[3], rn, a; };
-    __device__ void member(const Phys& ph, const DevState* d) {
-        this->NT = ph.NT;
-        dt = (T)d->dt;
-        inv_V = (T)ph.inv_V;
-        inv_h = (T)ph.inv_h;
-        rref = d->rho_ref;
-        bc = ph.bdf2 ? d->bdf : nullptr;
-        rm1 = ph.rm1;
-        inv_Vd = ph.inv_V;
-    }
-    __device__ void init(double* acc) const {
-        acc[0] = 0.0;
-        if (LAST) {
-            acc[1] = 0.0;
-            acc[2] = -__builtin_inf();
-        }
-    }
-    __device__ Pts load(size_t P) const {
-        return {{stream_ld(hbya + P), stream_ld(hbya + this->NT + P),
-                 stream_ld(hbya + 2 * this->NT + P)},
-                stream_ld(rn + P), stream_ld(aP + P)};
-    }
-    __device__ void cell(size_t P, const T (&v)[1][13], const T (&fp)[3], const T (&fm)[3],
-                         const Pts& p, double* acc) const {
-        T r, um[3];
-        corr_update_cell(v[0], fp, fm, p.hb, p.rn, p.a, dt, inv_V, inv_h, r, um);
-        if (bc) r = corr_rho_bdf2(fp, fm, p.rn, rm1[P], dt, inv_Vd, bc);
-        stream_st(rk + P, r);
-        double usq = 0.0;
-#pragma unroll
-        for (int m = 0; m < 3; ++m) {
-            stream_st(u + (m * this->NT + P), um[m]);
-            usq += (double)um[m] * (double)um[m];
-        }
-        if (LAST) {
-            acc[0] += (double)r;
-            acc[1] += usq;
-            const double nrho = -(rref + (double)r);
-            acc[2] = nrho > acc[2] ? nrho : acc[2];
-        }
-    }
-};
-
-template <typename T>
 struct TiledRefineFromZero : TiledBase<T> {
     static constexpr int NS = 2;          // w, d
     static constexpr int NR = 3;
@@ -4968,47 +4876,14 @@ void Ops<T>::helm_start(const Launch& L, hipStream_t s, const Phys& ph, DevState
     LAUNCH(k_helm_start<T>, L, s, ph, st, psidt, w, b, x, r, diag, part_u);
 }
 template <typename T>
-void Ops<T>::corr_flux(const Launch& L, const Launch& TL, hipStream_t s, const Phys& ph,
-                       const DevState* st, const T* p0, const T* x, const T* w, const T* phiH,
-                       T* phik, T* pt, double* snap_x) {
-    if (TL.nblocks) {
-        TiledCorrFlux<T> k{};
-        k.sf[0] = w;
-        k.sf[1] = p0;
-        k.sf[2] = x;
-        k.phiH = phiH;
-        k.phik = phik;
-        k.pt = pt;
-        k.snap_x = snap_x;
-        tiled_launch<T>(TL, s, ph, st, k);
-        return;
-    }
+void Ops<T>::corr_flux(const Launch& L, hipStream_t s, const Phys& ph, const T* p0, const T* x,
+                       const T* w, const T* phiH, T* phik, T* pt, double* snap_x) {
     LAUNCH(k_corr_flux<T>, L, s, ph, p0, x, w, phiH, phik, pt, snap_x);
 }
-template <typename T, bool LAST>
-static unsigned corr_update_tiled(const Launch& TL, hipStream_t s, const Phys& ph,
-                                  const DevState* st, const T* rn, const T* phik, const T* hb,
-                                  const T* pt, const T* aP, T* rk, T* u, double* part_mass) {
-    TiledCorrUpdate<T, LAST> k{};
-    k.sf[0] = pt;
-    k.face = phik;
-    k.part = part_mass;
-    k.rn = rn;
-    k.hbya = hb;
-    k.aP = aP;
-    k.rk = rk;
-    k.u = u;
-    return tiled_launch<T>(TL, s, ph, st, k);
-}
 template <typename T>
-unsigned Ops<T>::corr_update(const Launch& L, const Launch& TL, hipStream_t s, const Phys& ph,
-                             const DevState* st, bool last, const T* rn, const T* phik,
-                             const T* hb, const T* pt, const T* aP, T* rk, T* u,
-                             double* part_mass) {
-    if (TL.nblocks)
-        return last ? corr_update_tiled<T, true>(TL, s, ph, st, rn, phik, hb, pt, aP, rk, u, part_mass)
-                    : corr_update_tiled<T, false>(TL, s, ph, st, rn, phik, hb, pt, aP, rk, u,
-                                                  part_mass);
+unsigned Ops<T>::corr_update(const Launch& L, hipStream_t s, const Phys& ph, const DevState* st,
+                             bool last, const T* rn, const T* phik, const T* hb, const T* pt,
+                             const T* aP, T* rk, T* u, double* part_mass) {
     if (last)
         LAUNCH((k_corr_update<T, true>), L, s, ph, st, rn, phik, hb, pt, aP, rk, u, part_mass);
     else

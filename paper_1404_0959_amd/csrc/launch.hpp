@@ -290,23 +290,21 @@ struct Ops {
     static void helm_start(const Launch& L, hipStream_t s, const Phys& ph, DevState* st,
                            const T* psidt, const T* w, const T* b, const T* x, T* r, T* diag,
                            double* part_u);
-    static void corr_flux(const Launch& L, const Launch& TL, hipStream_t s, const Phys& ph,
-                          const DevState* st, const T* p0, const T* x, const T* w,
-                          const T* phiH, T* phik, T* pt, double* snap_x);
-    // corr_flux and corr_update in one tiled pass (TL.nblocks > 0), p not
+    static void corr_flux(const Launch& L, hipStream_t s, const Phys& ph, const T* p0, const T* x,
+                          const T* w, const T* phiH, T* phik, T* pt, double* snap_x);
+    // corr_flux and corr_update in one pass (TL: the tiled or the gathered launch), p not
     // stored; the last corrector writes, from part_mass on, columns of nb
     // partials each: the three of the mass budget, then the Courant maxima of
     // the new state (4 nb <= 4 max_blocks: within PS_MASS and PS_CFL).
-    // Returns nb, the launch's block count.
+    // Returns nb.
     static unsigned corr_finish_fused(const Launch& TL, hipStream_t s, const Phys& ph,
                                       const DevState* st, bool last, const T* p0, const T* x,
                                       const T* w, const T* phiH, T* phik, double* snap_x,
                                       const T* rn, const T* hb, const T* aP, T* rk, T* u,
                                       double* part_mass);
-    static unsigned corr_update(const Launch& L, const Launch& TL, hipStream_t s, const Phys& ph,
-                                const DevState* st, bool last, const T* rn, const T* phik,
-                                const T* hb, const T* pt, const T* aP, T* rk, T* u,
-                                double* part_mass);
+    static unsigned corr_update(const Launch& L, hipStream_t s, const Phys& ph, const DevState* st,
+                                bool last, const T* rn, const T* phik, const T* hb, const T* pt,
+                                const T* aP, T* rk, T* u, double* part_mass);
     static void dudt(const Launch& L, const Launch& TL, hipStream_t s, const Phys& ph,
                      const DevState* st, const T* un, const T* u1, T* acc);
     static void dust_flux(const Launch& L, const Launch& TL, hipStream_t s, const Phys& ph,

@@ -428,8 +428,10 @@ __global__ void __launch_bounds__(256) k_conv4_taps(int n, int batch, const uint
 // product are their 2 x 16 cells, lane group gq holding cells 8 (gq & 1) .. + 7
 // of row gq >> 1.  The four wavefronts' FP32 sums are added in FP64 and leave
 // as one FP64 partial per block; a block works on every kWgBlocks-th unit
-// (column, chunk of planes), so a sum runs over no more cells in FP32 than
-// with one wavefront per 1/1024 of the cells.  k_wgrad_total adds the partials
+// (column, chunk of planes), so a sum takes no more FP32 additions of products
+// than one of 16-cell products with a wavefront per 1/1024 of the cells (from 16^3 to
+// 256^3 and 64 grids; it may run over more cells, 32 against 16 for one grid of
+// 16^3).  k_wgrad_total adds the partials
 // of all layers, 16 slices of blocks at a time (one thread per entry walked them
 // all: 245 us a layer).  16 grids of 32^3: 22 us for a 16 -> 16 layer against
 // 65, 10 for the first and 9 for the last against 84 and 65, the totals of the
@@ -988,14 +990,6 @@ __global__ void k_adam(int nw, float* __restrict__ w, const float* __restrict__ 
 // ------------------------------------------------------------------------
 // host side
 // ------------------------------------------------------------------------
-static const int kCh[5] = {2, 16, 16, 16, 1};
-
-size_t net_weight_offset(int layer) {
-    size_t s = 0;
-    for (int l = 0; l < layer; ++l) s += (size_t)kCh[l] * kCh[l + 1] * 27;
-    return s;
-}
-
 size_t net_packed_bytes() { return offsetof(Packed, taps); }
 
 void net_pack_forward(hipStream_t s, const float* w32, void* wpk) {

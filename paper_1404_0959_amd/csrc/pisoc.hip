@@ -846,11 +846,11 @@ void enqueue_corr_finish(pisoc_ctx* ctx, StepPtrs<T>& S, int corr) {
         return;
     }
     timed(ctx, KC_CORR_FLUX, 10, -1, [&] {
-        O::corr_flux(L, ctx->TL, s, ph, ctx->st, S.p0, S.x, S.w, S.phiH, S.phik, S.q,
+        O::corr_flux(L, s, ph, S.p0, S.x, S.w, S.phiH, S.phik, S.q,
                      cap ? S.snap + 3 * N : nullptr);
     });
     timed(ctx, KC_CORR_UPDATE, 13, -1, [&] {
-        ctx->nb_mass = O::corr_update(L, ctx->TL, s, ph, ctx->st, last, S.rn, S.phik, S.hb, S.q,
+        ctx->nb_mass = O::corr_update(L, s, ph, ctx->st, last, S.rn, S.phik, S.hb, S.q,
                                       S.aP, S.rk, ucur, ctx->part(PS_MASS));
     });
 }
