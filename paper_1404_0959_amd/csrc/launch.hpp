@@ -43,6 +43,10 @@ Launch make_launch_shaped(int n, int batch, int bx, int cz);
 // them (seg_width) beyond; below 40 nblocks is 0.  Blocks march
 // over exactly min(cz_tile, n) planes when cz_tile > 0 (a tuned choice; the
 // default's own cz changes nothing).
+// The tiles against flattened rows or segments, us of a step's field kernels, tiles
+// first: FP32 128^3 573, 621; 192^3 1633, 1850; 256^3 3830, 5200; 320^3 7370, 8580; FP64
+// 192^3 2690, 2820; 256^3 6090, 6960; 320^3 12230, 12580; at 128^3 alone, and in FP64
+// alone, the rows are the faster (854, 788).
 // Flattened rows: as many as fit 512 threads (256 registers a thread in FP64), at
 // least 4, so that the y halo is no larger than the block's own rows: n <= 128.
 // Below n = 40 the gathered kernels are as fast (the launch's latency is all).
