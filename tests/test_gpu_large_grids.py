@@ -61,6 +61,7 @@ def flow(n, seed):
 
 @pytest.mark.parametrize("precision,n", [
     ("fp64", 290), ("fp64", 320), ("fp64", 336), ("fp32", 257), ("fp32", 320), ("fp32", 352), ("fp32", 385),
+    ("fp32", 528),
 ])
 def test_step_matches_gathered(P, monkeypatch, precision, n):
     """A step against the gathered kernels (PISOC_UNTILED=1), with the bounds of the same
